@@ -154,7 +154,7 @@ SUGG_API int32_t sugg_load_features(sugg_ctx* ctx, const sugg_plan* plan, const 
  * under graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, modes, results (bit-identical) and errors,
  * but the call allocates nothing.  The FP64 column-statistics partials of
- * SUGG_FIT_STATS (2 x E x min(1024, ceil(N / 256)) doubles) live in a static
+ * SUGG_FIT_STATS (2 x E x min(1024, ceil(N / 64)) doubles) live in a static
  * device array of SUGG_NOALLOC_SCRATCH_BYTES that the library holds on every
  * GPU it runs on until the process ends (its address is looked up by
  * sugg_create); a plan whose partials would not fit is rejected with

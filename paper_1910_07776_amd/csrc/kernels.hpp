@@ -174,11 +174,12 @@ hipError_t launch_confirm(int32_t K, int32_t n, int32_t* idx, float* plain, cons
                           const int32_t* band_idx, const float* band_plain, int32_t C, float tau, int32_t* flag,
                           hipStream_t s);
 
-// FP64 column statistics of x = ln(c / cyc) over all N rows.
+// FP64 column statistics of x = ln(c / cyc) over all N rows; lcyc (nullable,
+// [N]) receives every row's ln(cyc).
 template <typename T>
 hipError_t launch_colstats(const T* counters, const T* cycles, int64_t N, int32_t E,
                            double* partial, int32_t nchunks, double* mu64, double* sig64,
-                           T* mu_t, T* isg_t, int32_t* status, hipStream_t s);
+                           T* mu_t, T* isg_t, int32_t* status, hipStream_t s, double* lcyc = nullptr);
 int colstats_chunks(int64_t N);
 
 // z = (x - mu) / sigma in the plan dtype.

@@ -22,68 +22,105 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
 
 // ---- column statistics in FP64 -------------------------------------------
 // Each workgroup owns a contiguous chunk of rows; 16 lanes share a row and
-// each lane owns columns l16 + 16 i.  Sums of d = x - x(row 0) and d^2 are
-// accumulated per lane, combined across the 16 row groups in a fixed order,
-// and the chunks are combined in a fixed order by the final kernel, so the
-// result is bit-reproducible.
-constexpr int kMaxColsPerLane = 16;   // 256 events / 16 lanes
+// each lane owns VPL columns, read VW at a time (16 bytes where the rows are
+// aligned).  Sums of d = x - x(row 0) and d^2 are accumulated per lane,
+// combined across the 16 row groups in a fixed order, and the chunks are
+// combined in a fixed order by the final kernel, so the result is
+// bit-reproducible.  With lcyc, ln(cycles) of every row is written too.
+//
+// Bound by the FP64 logarithms (one per counter): with the library's log,
+// 16 columns a lane whatever E is and scalar loads, 4.8 M rows x 128 took
+// 3.06 ms and 32,768 rows 62 us; with flog64, VPL columns and vector loads
+// 1.11 ms and 15.9 us.
 constexpr int kStatThreads = 256;
 
+// Chunks of at least 64 rows (four per row group): 32,768 rows then give two
+// workgroups per compute unit; at most 1024, which bounds the partials.
 int colstats_chunks(int64_t N) {
-  int64_t c = (N + 255) / 256;
+  int64_t c = (N + 63) / 64;
   if (c > 1024) c = 1024;
   if (c < 1) c = 1;
   return (int)c;
 }
 
-template <typename T>
+template <typename T, int VPL, int VW>
 __global__ void __launch_bounds__(kStatThreads) colstats_partial_kernel(
     const T* __restrict__ c, const T* __restrict__ cyc, int64_t N, int E, int64_t rows_per_chunk,
-    double* __restrict__ partial, int32_t* status) {
+    double* __restrict__ partial, double* __restrict__ lcyc, int32_t* status) {
+  constexpr int NCH = VPL / VW;
   const int tid = threadIdx.x, l16 = tid & 15, grp = tid >> 4;
   const int64_t r0 = blockIdx.x * rows_per_chunk;
   const int64_t r1 = r0 + rows_per_chunk < N ? r0 + rows_per_chunk : N;
-  __shared__ double red[16][16][2];
-  const double lc0 = log((double)cyc[0]);
-  double sh[kMaxColsPerLane], s1[kMaxColsPerLane], s2[kMaxColsPerLane];
+  __shared__ double red[16][16 * VW][2];
+  auto load = [&](int64_t r, T (&v)[NCH][VW]) {
 #pragma unroll
-  for (int i = 0; i < kMaxColsPerLane; ++i) {
-    const int col = l16 + 16 * i;
-    sh[i] = col < E ? log((double)c[col]) - lc0 : 0.0;
-    s1[i] = 0.0;
-    s2[i] = 0.0;
-  }
-  bool bad = false;
-  for (int64_t r = r0 + grp; r < r1; r += 16) {
-    const double lc = log((double)cyc[r]);
-    const T* rp = c + r * E;
+    for (int ch = 0; ch < NCH; ++ch) {
+      const int c0 = (l16 + 16 * ch) * VW;
+      if (c0 < E) {
+        const VecN<T, VW> q = *reinterpret_cast<const VecN<T, VW>*>(c + r * E + c0);
 #pragma unroll
-    for (int i = 0; i < kMaxColsPerLane; ++i) {
-      const int col = l16 + 16 * i;
-      if (col < E) {
-        const double x = log((double)rp[col]) - lc;
-        bad |= !__builtin_isfinite(x);
-        const double d = x - sh[i];
-        s1[i] += d;
-        s2[i] = fma(d, d, s2[i]);
+        for (int v2 = 0; v2 < VW; ++v2) v[ch][v2] = q.v[v2];
+      } else {
+#pragma unroll
+        for (int v2 = 0; v2 < VW; ++v2) v[ch][v2] = T(1);
       }
     }
+  };
+  double sh[NCH][VW], s1[NCH][VW], s2[NCH][VW];
+  T cur[NCH][VW], nxt[NCH][VW];
+  load(0, cur);
+  const double lc0 = flog64((double)cyc[0]);
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+    for (int v = 0; v < VW; ++v) {
+      sh[ch][v] = flog64((double)cur[ch][v]) - lc0;
+      s1[ch][v] = 0.0;
+      s2[ch][v] = 0.0;
+    }
+  bool bad = false;
+  int64_t r = r0 + grp;
+  T cy = cyc[r < r1 ? r : r0], cyn = cy;
+  load(r < r1 ? r : r0, cur);
+  for (; r < r1; r += 16) {
+    const int64_t rn = r + 16 < r1 ? r + 16 : r;   // the next row's loads overlap this row's logarithms
+    load(rn, nxt);
+    cyn = cyc[rn];
+    const double lc = flog64((double)cy);
+    if (lcyc && l16 == 0) lcyc[r] = lc;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      const bool live = (l16 + 16 * ch) * VW < E;
+#pragma unroll
+      for (int v = 0; v < VW; ++v) {
+        const double x = flog64((double)cur[ch][v]) - lc;
+        bad |= live & !__builtin_isfinite(x);
+        const double d = x - sh[ch][v];
+        s1[ch][v] += d;
+        s2[ch][v] = fma(d, d, s2[ch][v]);
+        cur[ch][v] = nxt[ch][v];
+      }
+    }
+    cy = cyn;
   }
   if (__ballot(bad) != 0 && (tid & 63) == 0) atomicOr(status, (int)kStatusBadCounter);
   double* out = partial + (int64_t)blockIdx.x * 2 * E;
 #pragma unroll
-  for (int i = 0; i < kMaxColsPerLane; ++i) {
-    if (16 * i >= E) break;
-    red[grp][l16][0] = s1[i];
-    red[grp][l16][1] = s2[i];
+  for (int ch = 0; ch < NCH; ++ch) {
+    if (16 * ch * VW >= E) break;
+#pragma unroll
+    for (int v = 0; v < VW; ++v) {
+      red[grp][l16 * VW + v][0] = s1[ch][v];
+      red[grp][l16 * VW + v][1] = s2[ch][v];
+    }
     __syncthreads();
-    if (grp == 0) {
+    if (tid < 16 * VW) {
       double a = 0.0, b = 0.0;
       for (int g = 0; g < 16; ++g) {
-        a += red[g][l16][0];
-        b += red[g][l16][1];
+        a += red[g][tid][0];
+        b += red[g][tid][1];
       }
-      const int col = l16 + 16 * i;
+      const int col = 16 * ch * VW + tid;
       if (col < E) {
         out[col] = a;
         out[E + col] = b;
@@ -93,18 +130,33 @@ __global__ void __launch_bounds__(kStatThreads) colstats_partial_kernel(
   }
 }
 
+// One workgroup per 8 columns: 32 threads a column sum every 32nd chunk each
+// (four loads in flight), then their sums are added in order.
 template <typename T>
-__global__ void colstats_final_kernel(const T* __restrict__ c, const T* __restrict__ cyc, int64_t N,
+__global__ void __launch_bounds__(256) colstats_final_kernel(const T* __restrict__ c, const T* __restrict__ cyc, int64_t N,
                                       int E, const double* __restrict__ partial, int nchunks,
                                       double* mu64, double* sig64, T* mu_t, T* isg_t) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= E) return;
-  const double sh = log((double)c[j]) - log((double)cyc[0]);
+  __shared__ double red[32][8][2];
+  const int jl = threadIdx.x & 7, sl = threadIdx.x >> 3;
+  const int j = blockIdx.x * 8 + jl;
   double a = 0.0, b = 0.0;
-  for (int q = 0; q < nchunks; ++q) {
-    a += partial[(int64_t)q * 2 * E + j];
-    b += partial[(int64_t)q * 2 * E + E + j];
+  if (j < E) {
+#pragma unroll 4
+    for (int q = sl; q < nchunks; q += 32) {
+      a += partial[(int64_t)q * 2 * E + j];
+      b += partial[(int64_t)q * 2 * E + E + j];
+    }
   }
+  red[sl][jl][0] = a;
+  red[sl][jl][1] = b;
+  __syncthreads();
+  if (sl != 0 || j >= E) return;
+  a = b = 0.0;
+  for (int q = 0; q < 32; ++q) {
+    a += red[q][jl][0];
+    b += red[q][jl][1];
+  }
+  const double sh = flog64((double)c[j]) - flog64((double)cyc[0]);
   const double m = a / (double)N;
   double var = b / (double)N - m * m;
   if (var < 0.0) var = 0.0;
@@ -120,16 +172,27 @@ __global__ void colstats_final_kernel(const T* __restrict__ c, const T* __restri
 template <typename T>
 hipError_t launch_colstats(const T* counters, const T* cycles, int64_t N, int32_t E, double* partial,
                            int32_t nchunks, double* mu64, double* sig64, T* mu_t, T* isg_t,
-                           int32_t* status, hipStream_t s) {
+                           int32_t* status, hipStream_t s, double* lcyc) {
   if (N <= 0) return hipErrorInvalidValue;
   const int64_t per = (N + nchunks - 1) / nchunks;
   const int used = (int)((N + per - 1) / per);
+  constexpr int VEC = 16 / sizeof(T);
+  const bool vec = E % VEC == 0 && reinterpret_cast<uintptr_t>(counters) % 16 == 0;
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(colstats_partial_kernel<T>, dim3(used), dim3(kStatThreads), 0, s, counters,
-                     cycles, N, (int)E, per, partial, status);
+  auto run = [&](auto vpl, auto vw) {
+    hipLaunchKernelGGL((colstats_partial_kernel<T, decltype(vpl)::value, decltype(vw)::value>), dim3(used),
+                       dim3(kStatThreads), 0, s, counters, cycles, N, (int)E, per, partial, lcyc, status);
+  };
+  using std::integral_constant;
+  if (vec && E <= 64) run(integral_constant<int, 4>{}, integral_constant<int, VEC>{});
+  else if (vec && E <= 128) run(integral_constant<int, 8>{}, integral_constant<int, VEC>{});
+  else if (vec) run(integral_constant<int, 16>{}, integral_constant<int, VEC>{});
+  else if (E <= 64) run(integral_constant<int, 4>{}, integral_constant<int, 1>{});
+  else if (E <= 128) run(integral_constant<int, 8>{}, integral_constant<int, 1>{});
+  else run(integral_constant<int, 16>{}, integral_constant<int, 1>{});
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(colstats_final_kernel<T>, dim3((E + 255) / 256), dim3(256), 0, s, counters, cycles,
+  hipLaunchKernelGGL(colstats_final_kernel<T>, dim3((E + 7) / 8), dim3(256), 0, s, counters, cycles,
                      N, (int)E, partial, used, mu64, sig64, mu_t, isg_t);
   return hipGetLastError();
 }
@@ -398,7 +461,7 @@ hipError_t launch_confirm(int32_t K, int32_t n, int32_t* idx, float* plain, cons
 
 #define SUGG_INST(T)                                                                                     \
   template hipError_t launch_colstats<T>(const T*, const T*, int64_t, int32_t, double*, int32_t, double*, \
-                                         double*, T*, T*, int32_t*, hipStream_t);                         \
+                                         double*, T*, T*, int32_t*, hipStream_t, double*);                \
   template hipError_t launch_standardize<T>(const T*, const T*, int64_t, int32_t, const T*, const T*, T*, \
                                             int32_t*, hipStream_t);                                       \
   template hipError_t launch_standardize_rows<T>(const T*, const T*, const int64_t*, int64_t, int32_t, const T*, \
