@@ -207,58 +207,147 @@ int ensure_stat_ws(sugg_ctx* ctx, sugg_plan* p) {
                   "statistics workspace");
 }
 
-int prepare_fit(sugg_ctx* ctx, sugg_plan* p) {
-  if (p->fit_ready) return SUGG_OK;
-  const int E = p->E, D = p->D;
-  // per-optimisation list of (kernel, local bit); pair space prefix sums
-  std::vector<std::vector<std::pair<int, int>>> lists(D);
+// Whether the fit takes each row once for the set ("class") of optimisations
+// it is a before version of, instead of once per optimisation.  A class costs
+// a partial sum of its own, the pair list B/2 times the rows: with u ids in
+// use there are up to 2^u classes, taken when they hold 32 rows or more on
+// average.  Whole fits, classes against pairs, 128 events, ten ids, 4..10 per
+// kernel: 18 rows a class (64 kernels) 479 against 456 us, 37 rows 489
+// against 517, 147 rows 577 against 820, 590 rows 993 against 2415; six ids
+// (64 classes): 16 rows 397 against 409 us; 40 events, ten ids, 6 per kernel:
+// 8 rows 176 against 155 us, 32 rows 183 against 178.
+bool gram_classes(int64_t rows, int used_ids) {
+  return used_ids < 40 && ((int64_t)1 << used_ids) <= rows / 32;
+}
+
+// The row list of the fit in segments, and the optimisations of each run of
+// segments (mask, first entry).
+struct GramLists {
+  std::vector<GramSeg> segs;
+  std::vector<int32_t> klist;
+  std::vector<std::pair<uint64_t, int64_t>> runs;
+  int64_t n = 0;
+  bool pairs = false;
+};
+
+void gram_pair_lists(const sugg_plan* p, GramLists& g) {
+  g.pairs = true;
+  std::vector<std::vector<std::pair<int, int>>> lists(p->D);   // (kernel, local bit) per id
   for (int k = 0; k < p->K; ++k)
     for (int b = 0; b < p->nopts[k]; ++b) lists[p->opt_ids[p->opt_off[k] + b]].push_back({k, b});
-  int64_t total = 0;
-  for (int o = 0; o < D; ++o) total += p->opt_pairs[o];
-  const int target_items = 4 * cu_count(ctx->device);
-  int64_t chunk = total / std::max(1, target_items);
-  chunk = std::max<int64_t>(chunk, 256);
-  chunk = (chunk + 31) / 32 * 32;
-  std::vector<int64_t> pbase, prow0;
-  std::vector<int32_t> pbit, owb(D + 1, 0);
-  std::vector<GramWork> work;
-  for (int o = 0; o < D; ++o) {
-    owb[o] = (int)work.size();
-    const int lb = (int)pbase.size();
-    int64_t acc = 0;
+  for (int o = 0; o < p->D; ++o) {
+    if (lists[o].empty()) continue;
+    g.runs.push_back({1ull << o, g.n});
     for (auto& kb : lists[o]) {
-      pbase.push_back(acc);
-      prow0.push_back(p->row_off[kb.first]);
-      pbit.push_back(kb.second);
-      acc += (int64_t)1 << (p->nopts[kb.first] - 1);
-    }
-    const int le = (int)pbase.size();
-    for (int64_t s0 = 0; s0 < acc; s0 += chunk) {
-      GramWork w;
-      w.opt = o;
-      w.list_begin = lb;
-      w.list_end = le;
-      w.pad = 0;
-      w.s_begin = s0;
-      w.s_end = std::min(acc, s0 + chunk);
-      work.push_back(w);
+      g.segs.push_back(GramSeg{g.n, kb.first, kb.second, (uint64_t)kb.second});
+      g.n += (int64_t)1 << (p->nopts[kb.first] - 1);
     }
   }
-  owb[D] = (int)work.size();
+}
+
+// Kernels with the same ids form a group; version S of a group's kernels is a
+// segment of the class "the group's ids without S's".  Segments in class
+// order (by compressed mask), groups by first kernel within a class.
+void gram_class_lists(const sugg_plan* p, GramLists& g) {
+  std::vector<uint64_t> kmask(p->K, 0);
+  uint64_t used = 0;
+  for (int k = 0; k < p->K; ++k) {
+    for (int64_t i = p->opt_off[k]; i < p->opt_off[k + 1]; ++i) kmask[k] |= 1ull << p->opt_ids[i];
+    used |= kmask[k];
+  }
+  int at[64], n_used = 0;      // compressed position of an id
+  for (int o = 0; o < 64; ++o)
+    if ((used >> o) & 1) at[o] = n_used++;
+  g.klist.resize(p->K);
+  for (int k = 0; k < p->K; ++k) g.klist[k] = k;
+  std::stable_sort(g.klist.begin(), g.klist.end(), [&](int a, int b) { return kmask[a] < kmask[b]; });
+  // two passes over (group, version): count the classes' segments, place them
+  const int64_t n_cls = (int64_t)1 << n_used;
+  std::vector<int64_t> begin(n_cls + 1, 0);
+  auto sweep = [&](auto&& f) {
+    for (int i = 0; i < p->K;) {
+      int j = i + 1;
+      const uint64_t m = kmask[g.klist[i]];
+      while (j < p->K && kmask[g.klist[j]] == m) ++j;
+      const int k = g.klist[i], B = p->nopts[k];
+      const int32_t* ids = p->opt_ids.data() + p->opt_off[k];
+      for (int S = 0; S + 1 < (1 << B); ++S) {   // the version with everything applied is before nothing
+        uint64_t cm = 0, bits = 0;
+        int n = 0;
+        for (int b = 0; b < B; ++b)
+          if (!((S >> b) & 1)) {
+            cm |= 1ull << at[ids[b]];
+            bits |= (uint64_t)b << (4 * n++);
+          }
+        f(cm, i, j - i, S, bits);
+      }
+      i = j;
+    }
+  };
+  sweep([&](uint64_t cm, int, int, int, uint64_t) { ++begin[cm + 1]; });
+  for (int64_t c = 0; c < n_cls; ++c) begin[c + 1] += begin[c];
+  g.segs.resize(begin[n_cls]);
+  std::vector<int64_t> put(begin.begin(), begin.end() - 1);
+  std::vector<int32_t> count(g.segs.size());
+  sweep([&](uint64_t cm, int first, int nk, int S, uint64_t bits) {
+    count[put[cm]] = nk;
+    g.segs[put[cm]++] = GramSeg{0, first, S, bits};
+  });
+  for (int64_t c = 0; c < n_cls; ++c) {
+    if (begin[c] == begin[c + 1]) continue;
+    uint64_t mask = 0;
+    for (int o = 0; o < 64; ++o)
+      if (((used >> o) & 1) && ((c >> at[o]) & 1)) mask |= 1ull << o;
+    g.runs.push_back({mask, g.n});
+    for (int64_t i = begin[c]; i < begin[c + 1]; ++i) {
+      g.segs[i].base = g.n;
+      g.n += count[i];
+    }
+  }
+}
+
+int prepare_fit(sugg_ctx* ctx, sugg_plan* p, hipStream_t s) {
+  if (p->fit_ready) return SUGG_OK;
+  const int E = p->E, D = p->D;
+  GramLists g;
+  int used = 0;
+  for (int o = 0; o < D; ++o) used += p->opt_pairs[o] > 0;
+  if (gram_classes(p->N, used)) gram_class_lists(p, g);
+  else gram_pair_lists(p, g);
+  // Chunks: two per compute unit, of at least 128 rows (a chunk's partial
+  // sum, written and read back, costs about as much as 150 rows) and at most
+  // 2304 (so that the last ones to run are short); largest first.
+  const int64_t want = (g.n + 2 * cu_count(ctx->device) - 1) / (2 * cu_count(ctx->device));
+  const int64_t chunk = std::min<int64_t>(std::max<int64_t>((want + 31) / 32 * 32, 128), 2304);
+  std::vector<GramWork> work;
+  for (size_t r = 0; r < g.runs.size(); ++r) {
+    const int64_t e = r + 1 < g.runs.size() ? g.runs[r + 1].second : g.n;
+    for (int64_t b = g.runs[r].second; b < e; b += chunk)
+      work.push_back(GramWork{b, g.runs[r].first, (int32_t)std::min(chunk, e - b), 0});
+  }
+  std::stable_sort(work.begin(), work.end(), [](const GramWork& x, const GramWork& y) { return x.n > y.n; });
+  const size_t stride = (size_t)gram_stride(E);
+  GramSeg* d_segs = nullptr;
+  int32_t* d_klist = nullptr;
   hipError_t e = hipSuccess;
-  const size_t stride = (size_t)E * E + 2 * E + 2;
-  if (e == hipSuccess) e = hipMalloc((void**)&p->d_z64, sizeof(double) * std::max<int64_t>(1, p->N * E));
-  if (e == hipSuccess) e = hipMalloc((void**)&p->d_lcyc64, sizeof(double) * std::max<int64_t>(1, p->N));
-  if (e == hipSuccess) e = hipMalloc((void**)&p->d_gram_partial, sizeof(double) * stride * std::max<size_t>(1, work.size()));
-  if (e == hipSuccess) e = hipMalloc((void**)&p->d_reduced, sizeof(double) * stride * std::max(1, D));
-  if (e == hipSuccess && sizeof(double) * (size_t)(E + 1) * (E + 1) > 150 * 1024)
-    e = hipMalloc((void**)&p->d_solveA, sizeof(double) * (size_t)(E + 1) * (E + 1) * std::max(1, D));
-  if (e == hipSuccess) e = upload(p->d_gwork, work.data(), sizeof(GramWork) * work.size());
-  if (e == hipSuccess) e = upload(p->d_pair_base, pbase.data(), sizeof(int64_t) * pbase.size());
-  if (e == hipSuccess) e = upload(p->d_pair_row0, prow0.data(), sizeof(int64_t) * prow0.size());
-  if (e == hipSuccess) e = upload(p->d_pair_bit, pbit.data(), sizeof(int32_t) * pbit.size());
-  if (e == hipSuccess) e = upload(p->d_opt_work_begin, owb.data(), sizeof(int32_t) * owb.size());
+  auto A = [&](auto*& q, size_t bytes) {
+    if (e == hipSuccess && !q) e = hipMalloc((void**)&q, std::max<size_t>(bytes, 16));
+  };
+  A(p->d_lcyc64, sizeof(double) * p->N);
+  A(p->d_gram_partial, sizeof(double) * stride * work.size());
+  A(p->d_gram_slices, sizeof(double) * stride * D * gram_slices((int)work.size()));
+  A(p->d_reduced, sizeof(double) * stride * D);
+  A(p->d_grows, sizeof(GramRow) * g.n);
+  if (sizeof(double) * (size_t)(E + 1) * (E + 1) > 150 * 1024)
+    A(p->d_solveA, sizeof(double) * (size_t)(E + 1) * (E + 1) * std::max(1, D));
+  if (e == hipSuccess && !p->d_gwork) e = upload(p->d_gwork, work.data(), sizeof(GramWork) * work.size());
+  if (e == hipSuccess) e = upload(d_segs, g.segs.data(), sizeof(GramSeg) * g.segs.size());
+  if (e == hipSuccess) e = upload(d_klist, g.klist.data(), sizeof(int32_t) * g.klist.size());
+  if (e == hipSuccess)
+    e = launch_gram_rows(d_segs, (int)g.segs.size(), g.n, g.pairs, d_klist, p->d_row_off, p->d_grows, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);   // the segments are freed
+  dfree(d_segs);
+  dfree(d_klist);
   if (e != hipSuccess) return ctx->hip(e, "fit workspace");
   p->n_gwork = (int)work.size();
   p->fit_ready = true;
@@ -267,7 +356,7 @@ int prepare_fit(sugg_ctx* ctx, sugg_plan* p) {
 
 template <typename T>
 int run_fit(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, hipStream_t s) {
-  int rc = prepare_fit(ctx, p);
+  int rc = prepare_fit(ctx, p, s);
   if (!rc) rc = ensure_stat_ws(ctx, p);
   if (rc) return rc;
   rc = ctx->ensure_model(p->E, p->D);
@@ -275,7 +364,7 @@ int run_fit(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, hipStream_t s
   T* mu_t = (T*)(sizeof(T) == 4 ? (void*)ctx->mu32 : (void*)ctx->mu64);
   T* isg_t = (T*)(sizeof(T) == 4 ? (void*)ctx->isg32 : (void*)ctx->isg64);
   rc = ctx->hip(launch_colstats<T>(c, cyc, p->N, p->E, p->d_stat_partial, p->stat_chunks, ctx->mu64,
-                                   ctx->sig64, mu_t, isg_t, ctx->d_status, s), "column statistics");
+                                   ctx->sig64, mu_t, isg_t, ctx->d_status, s, p->d_lcyc64), "column statistics");
   if (rc) return rc;
   (void)hipGetLastError();
   hipLaunchKernelGGL(inv_kernel, dim3((p->E + 255) / 256), dim3(256), 0, s, ctx->sig64, ctx->isg64, p->E);
@@ -283,25 +372,23 @@ int run_fit(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, hipStream_t s
                      ctx->mu32, ctx->isg32, p->E);
   rc = ctx->hip(hipGetLastError(), "statistics");
   if (rc) return rc;
-  rc = ctx->hip(launch_zfeat64<T>(c, cyc, p->N, p->E, ctx->mu64, ctx->sig64, p->d_z64, p->d_lcyc64, s), "features");
-  if (rc) return rc;
   GramArgs g;
-  g.z64 = p->d_z64;
-  g.lcyc64 = p->d_lcyc64;
+  g.counters = c;
+  g.lcyc = p->d_lcyc64;
+  g.mu = ctx->mu64;
+  g.sig = ctx->sig64;
   g.E = p->E;
+  g.rows = p->d_grows;
   g.work = p->d_gwork;
   g.n_work = p->n_gwork;
-  g.pair_base = p->d_pair_base;
-  g.pair_row0 = p->d_pair_row0;
-  g.pair_bit = p->d_pair_bit;
   g.partial = p->d_gram_partial;
-  rc = ctx->hip(launch_gram(g, s), "gram");
+  rc = ctx->hip(launch_gram<T>(g, s), "gram");
+  if (!rc) rc = ctx->hip(launch_gram_reduce(g, p->D, p->d_gram_slices, p->d_reduced, s), "gram");
   if (rc) return rc;
   SolveArgs sa;
-  sa.partial = p->d_gram_partial;
-  sa.opt_work_begin = p->d_opt_work_begin;
   sa.E = p->E;
   sa.D = p->D;
+  sa.nb = gram_blocks(p->E);
   sa.lambda = ctx->params.lambda;
   sa.A = p->d_solveA;
   sa.reduced = p->d_reduced;

@@ -6,155 +6,326 @@
 // over every pair (version S without o, version S with o) of the training
 // kernels, accumulated and solved in FP64.
 //
-// gram_kernel   one workgroup per chunk of one optimisation's pairs: stages
-//               32 samples' z rows in LDS, each thread accumulates an 8x8
-//               register block of Z^T Z (plus the column sums for the
-//               intercept row and X^T y); the partial goes to a workspace.
-// solve_kernel  one workgroup per optimisation: sums its chunks in a fixed
-//               order, adds the ridge term, factorises A = L L^T (right-looking,
-//               in LDS when it fits) and solves two triangular systems.
+// gram_kernel         one workgroup per chunk of rows: Tier 1's features of a
+//                     stage of rows go to LDS with the labels and a column of
+//                     ones beside them, and the lower triangle of
+//                     [Z | Y | 1]^T [Z | Y | 1] is accumulated by the FP64
+//                     matrix cores; the partial goes to a workspace.
+// gram_reduce_kernel  sums the chunks of every optimisation, in a fixed order.
+// solve_kernel        one workgroup per optimisation: ridge term, Cholesky and
+//                     two triangular solves.
+#include <algorithm>
+
 #include "kernels.hpp"
+#include "path_impl.hpp"
 
 namespace sugg {
 
-constexpr int kGramThreads = 256;
-constexpr int kGramStage = 32;
-constexpr int kBlk = 8;
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+constexpr int kGramStage = 32;   // rows per stage
 
 __device__ __forceinline__ int64_t insert_zero_bit(int64_t q, int b) {
   return ((q >> b) << (b + 1)) | (q & ((1ll << b) - 1));
 }
 
-__global__ void __launch_bounds__(kGramThreads) gram_kernel(const GramArgs a) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int E = a.E;
-  double* zs = reinterpret_cast<double*>(smem);            // [kGramStage][E]
-  double* ys = zs + kGramStage * E;                          // [kGramStage]
-  int64_t* rows = reinterpret_cast<int64_t*>(ys + kGramStage);
-  const GramWork w = a.work[blockIdx.x];
-  const int tid = threadIdx.x;
-  const int nb = (E + kBlk - 1) / kBlk;
-  const int nblocks = nb * (nb + 1) / 2;   // blocks on and below the diagonal (Z^T Z is symmetric)
-  const int64_t stride = (int64_t)E * E + 2 * E + 2;
-  double* out = a.partial + (int64_t)blockIdx.x * stride;
-
-  // column sums (first pass only): thread j < E owns column j
-  double cz = 0.0, czy = 0.0, sy = 0.0;
-  const int64_t ns = w.s_end - w.s_begin;
-
-  for (int pass = 0; pass * kGramThreads < nblocks; ++pass) {
-    const int blk = pass * kGramThreads + tid;
-    const bool active = blk < nblocks;
-    // lower-triangle block t = bi (bi + 1) / 2 + bj, bj <= bi
-    int bi = 0, bj = 0;
-    if (active) {
-      bi = (int)((sqrt(8.0 * blk + 1.0) - 1.0) * 0.5);
-      while (bi * (bi + 1) / 2 > blk) --bi;
-      while ((bi + 1) * (bi + 2) / 2 <= blk) ++bi;
-      bj = blk - bi * (bi + 1) / 2;
+// The rows of every segment, in order (built once per plan).
+__global__ void __launch_bounds__(256) gram_rows_kernel(const GramSeg* __restrict__ segs, int nseg, int64_t n,
+                                                        int pairs, const int32_t* __restrict__ klist,
+                                                        const int64_t* __restrict__ row_off,
+                                                        GramRow* __restrict__ out) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    int lo = 0, hi = nseg - 1;
+    while (lo < hi) {   // last segment with base <= i
+      const int mid = (lo + hi + 1) >> 1;
+      if (segs[mid].base <= i) lo = mid;
+      else hi = mid - 1;
     }
-    double acc[kBlk][kBlk];
-#pragma unroll
-    for (int i = 0; i < kBlk; ++i)
-#pragma unroll
-      for (int j = 0; j < kBlk; ++j) acc[i][j] = 0.0;
-
-    for (int64_t s0 = 0; s0 < ns; s0 += kGramStage) {
-      const int cnt = (int)((ns - s0) < kGramStage ? (ns - s0) : kGramStage);
-      if (tid < cnt) {
-        const int64_t s = w.s_begin + s0 + tid;
-        int lo = w.list_begin, hi = w.list_end - 1;
-        while (lo < hi) {   // last entry with pair_base <= s
-          const int mid = (lo + hi + 1) >> 1;
-          if (a.pair_base[mid] <= s) lo = mid; else hi = mid - 1;
-        }
-        const int b = a.pair_bit[lo];
-        const int64_t S = insert_zero_bit(s - a.pair_base[lo], b);
-        const int64_t row = a.pair_row0[lo] + S;
-        rows[tid] = row;
-        ys[tid] = a.lcyc64[row] - a.lcyc64[row + (1ll << b)];
-      }
-      __syncthreads();
-      for (int i = tid; i < cnt * E; i += kGramThreads) {
-        const int q = i / E, j = i - q * E;
-        zs[i] = a.z64[rows[q] * E + j];
-      }
-      __syncthreads();
-      if (active) {
-        for (int q = 0; q < cnt; ++q) {
-          const double* zq = zs + q * E;
-          double zi[kBlk], zj[kBlk];
-#pragma unroll
-          for (int i = 0; i < kBlk; ++i) {
-            const int ci = bi * kBlk + i, cj = bj * kBlk + i;
-            zi[i] = ci < E ? zq[ci] : 0.0;
-            zj[i] = cj < E ? zq[cj] : 0.0;
-          }
-#pragma unroll
-          for (int i = 0; i < kBlk; ++i)
-#pragma unroll
-            for (int j = 0; j < kBlk; ++j) acc[i][j] = fma(zi[i], zj[j], acc[i][j]);
-        }
-      }
-      if (pass == 0) {
-        for (int j = tid; j < E; j += kGramThreads) {
-          // a thread owns at most one column when E <= 256
-          for (int q = 0; q < cnt; ++q) {
-            const double zv = zs[q * E + j];
-            cz += zv;
-            czy = fma(zv, ys[q], czy);
-          }
-        }
-        if (tid == 0)
-          for (int q = 0; q < cnt; ++q) sy += ys[q];
-      }
-      __syncthreads();
-    }
-    if (active) {
-#pragma unroll
-      for (int i = 0; i < kBlk; ++i)
-#pragma unroll
-        for (int j = 0; j < kBlk; ++j) {
-          const int ci = bi * kBlk + i, cj = bj * kBlk + j;
-          if (ci < E && cj < E) out[(int64_t)ci * E + cj] = acc[i][j];
-        }
-    }
-  }
-  for (int j = tid; j < E; j += kGramThreads) {
-    out[(int64_t)E * E + j] = cz;
-    out[(int64_t)E * E + E + j] = czy;
-  }
-  if (tid == 0) {
-    out[(int64_t)E * E + 2 * E] = sy;
-    out[(int64_t)E * E + 2 * E + 1] = (double)ns;
+    const GramSeg g = segs[lo];
+    const int64_t q = i - g.base;
+    GramRow r;
+    r.row = pairs ? row_off[g.first] + insert_zero_bit(q, g.sel) : row_off[klist[g.first + q]] + g.sel;
+    r.bits = g.bits;
+    out[i] = r;
   }
 }
 
-hipError_t launch_gram(const GramArgs& a, hipStream_t s) {
-  if (a.n_work <= 0) return hipSuccess;
-  const size_t smem = sizeof(double) * ((size_t)kGramStage * a.E + kGramStage) + sizeof(int64_t) * kGramStage;
-  if (smem > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gram_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
+hipError_t launch_gram_rows(const GramSeg* segs, int nseg, int64_t n, bool pairs, const int32_t* klist,
+                            const int64_t* row_off, GramRow* out, hipStream_t s) {
+  if (n <= 0 || nseg <= 0) return hipSuccess;
+  int64_t blocks = (n + 255) / 256;
+  if (blocks > 8192) blocks = 8192;
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(gram_kernel, dim3(a.n_work), dim3(kGramThreads), smem, s, a);
+  hipLaunchKernelGGL(gram_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, s, segs, nseg, n, pairs ? 1 : 0, klist,
+                     row_off, out);
   return hipGetLastError();
 }
 
-// Sum the partials of each optimisation's chunks in a fixed order; adjacent
-// threads read adjacent words of a chunk's partial.
+// Sixteen-column blocks of [Z | Y | 1]: E padded, and one block of 16 for the
+// labels (columns 0..11, the row's optimisations in ascending id) and the
+// ones (column kGramOnes).
+constexpr int kGramOnes = 12;
+static_assert(SUGG_MAX_OPTS <= kGramOnes, "label columns");
+int gram_blocks(int E) { return E <= 64 ? 5 : E <= 128 ? 9 : 17; }
+int64_t gram_stride(int E) { return (int64_t)gram_blocks(E) * (gram_blocks(E) + 1) / 2 * 256; }
+
+// One work item: rows [begin, begin + n) of the row list, all of them before
+// versions of the optimisations in `mask`.  A stage's rows are read from HBM
+// (16 lanes a row), standardised and laid out in LDS as [row][column]; the
+// block product of 16 columns by 16 columns over four rows is one
+// v_mfma_f64_16x16x4_f64, whose A and B operands have the same lane layout
+// (lane l: column l % 16 of row l / 16), so a 16-column operand serves as
+// either.  The block rows of the lower triangle are dealt out to V waves from
+// the longest down and back up, so each has about the same number of blocks
+// (9 block columns: 12, 11, 11, 11 of 45); beyond 128 events two workgroups
+// share an item's block rows.  The next stage's counters are in flight while
+// the matrix cores work on this one, in the other half of the LDS.
+//
+// Bound by the FP64 matrix rate (73 TFLOP/s measured; the FP64 vector rate is
+// the same, but there every 64 multiply-adds of an 8 x 8 register block cost
+// 16 LDS reads) and the logarithms.  A row enters once, however many
+// optimisations it is a before version of, where there are enough rows per
+// set of optimisations (gram_classes): 4.8 M rows in place of 21.5 M pairs on
+// the 16,384-kernel training set.  Features are formed here: their FP64 copy
+// (4.9 GB there) was written once and read back 4.5 times.
+// Measured on that set: 2.99 ms, where features and sums took 48.8 ms before;
+// 512 kernels of 64 versions: 38 us, before 223 us.
+template <typename T, int NB, int VW>
+__global__ void __launch_bounds__(NB <= 9 ? 256 : 512, 2) gram_kernel(const GramArgs a) {
+  constexpr int W = NB <= 9 ? 4 : 8;            // waves per workgroup
+  constexpr int V = NB <= 9 ? 4 : 16;           // waves that share an item's blocks (V / W workgroups)
+  constexpr int LD = 16 * NB;                   // LDS row, doubles: NB odd, so two rows differ by 32 banks
+  constexpr int NCH = (NB - 1) / VW;            // column chunks per lane
+  constexpr int RP = W * 4;                     // rows per pass of the workgroup
+  constexpr int NP = kGramStage / RP;           // passes per stage
+  constexpr int N1 = NB > V ? NB - V : 0, N2 = NB > 2 * V ? NB - 2 * V : 0;
+  static_assert(NB % 2 == 1 && (NB - 1) % VW == 0 && kGramStage % RP == 0, "stage shape");
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* zs = reinterpret_cast<double*>(smem);            // [2][kGramStage][LD]
+  double* cmu = zs + 2 * kGramStage * LD;                  // [16 (NB - 1)] column means, then 1 / sigma
+  double* cis = cmu + 16 * (NB - 1);
+  const int E = a.E;
+  const GramWork w = a.work[blockIdx.x];
+  const int tid = threadIdx.x, lane = tid & 63, l16 = tid & 15, rg = tid >> 4;
+  const int v = blockIdx.y * W + (tid >> 6);               // which share of the block rows
+  const int nids = __popcll(w.mask);
+  for (int j = tid; j < 16 * (NB - 1); j += 64 * W) {
+    cmu[j] = j < E ? a.mu[j] : 0.0;
+    cis[j] = j < E ? 1.0 / a.sig[j] : 0.0;
+  }
+  const int nst = (w.n + kGramStage - 1) / kGramStage;
+  const T* counters = reinterpret_cast<const T*>(a.counters);
+  T cnt[NP][NCH][VW];
+  double lc[NP], ly[NP];
+  GramRow ent[NP];
+  // list entries of a stage; past the item its last row is read again (and
+  // enters as zeros)
+  auto rows = [&](int st) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int r = st * kGramStage + p * RP + rg;
+      ent[p] = a.rows[w.begin + (r < w.n ? r : w.n - 1)];
+    }
+  };
+  auto load = [&]() {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const T* rp = counters + ent[p].row * E;
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        const int c0 = (l16 + 16 * ch) * VW;
+        if (c0 < E) {
+          const VecN<T, VW> q = *reinterpret_cast<const VecN<T, VW>*>(rp + c0);
+#pragma unroll
+          for (int u = 0; u < VW; ++u) cnt[p][ch][u] = q.v[u];
+        } else {
+#pragma unroll
+          for (int u = 0; u < VW; ++u) cnt[p][ch][u] = T(1);
+        }
+      }
+      lc[p] = a.lcyc[ent[p].row];
+      // lane j of the row: the after version of the row's j-th optimisation
+      const int bit = (int)(ent[p].bits >> (4 * l16)) & 15;
+      ly[p] = a.lcyc[ent[p].row + (l16 < nids ? (int64_t)1 << bit : 0)];
+    }
+  };
+  auto store = [&](int st, double* buf) {
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int rr = p * RP + rg;
+      const bool live = st * kGramStage + rr < w.n;
+      double* zr = buf + rr * LD;
+#pragma unroll
+      for (int ch = 0; ch < NCH; ++ch) {
+        const int c0 = (l16 + 16 * ch) * VW;
+        VecN<double, VW> q;
+#pragma unroll
+        for (int u = 0; u < VW; ++u) {
+          const double x = flog64((double)cnt[p][ch][u]) - lc[p];
+          q.v[u] = live && c0 + u < E ? (x - cmu[c0 + u]) * cis[c0 + u] : 0.0;
+        }
+        *reinterpret_cast<VecN<double, VW>*>(zr + c0) = q;
+      }
+      zr[16 * (NB - 1) + l16] = !live ? 0.0 : l16 < nids ? lc[p] - ly[p] : l16 == kGramOnes ? 1.0 : 0.0;
+    }
+  };
+  // this wave's block rows: NB-1-v, NB-2V+v and NB-1-2V-v, where they exist
+  const int r0 = NB - 1 - v, r1 = NB - 2 * V + v;
+  doublex4 acc0[NB], acc1[N1 > 0 ? N1 : 1], acc2[1];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) acc0[j] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < (N1 > 0 ? N1 : 1); ++j) acc1[j] = doublex4{0.0, 0.0, 0.0, 0.0};
+  acc2[0] = doublex4{0.0, 0.0, 0.0, 0.0};
+  static_assert(N2 <= 1, "third block rows");
+
+  rows(0);
+  load();
+  if (nst > 1) rows(1);
+  __syncthreads();   // column constants
+  store(0, zs);
+  __syncthreads();
+  for (int st = 0; st < nst; ++st) {
+    const double* buf = zs + (st & 1) * kGramStage * LD;
+    if (st + 1 < nst) {
+      load();
+      if (st + 2 < nst) rows(st + 2);
+    }
+#pragma unroll 2
+    for (int k = 0; k < kGramStage; k += 4) {
+      const double* zk = buf + (k + (lane >> 4)) * LD + l16;
+      double b[NB];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) b[j] = zk[16 * j];
+      const double a0 = zk[16 * r0];
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (j <= r0) acc0[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b[j], acc0[j], 0, 0, 0);
+      if (N1 > 0 && r1 >= 0) {
+        const double a1 = zk[16 * r1];
+#pragma unroll
+        for (int j = 0; j < N1; ++j)
+          if (j <= r1) acc1[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b[j], acc1[j], 0, 0, 0);
+      }
+      if (N2 > 0 && v == 0) acc2[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(b[0], b[0], acc2[0], 0, 0, 0);
+    }
+    if (st + 1 < nst) store(st + 1, zs + ((st + 1) & 1) * kGramStage * LD);
+    __syncthreads();
+  }
+  // element i of lane l: row 4 i + l / 16, column l % 16 of the block
+  double* out = a.partial + (int64_t)blockIdx.x * (NB * (NB + 1) / 2 * 256);
+  auto put = [&](int bi, int bj, const doublex4& c) {
+    double* o = out + (bi * (bi + 1) / 2 + bj) * 256 + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[64 * i] = c[i];
+  };
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (j <= r0) put(r0, j, acc0[j]);
+  if (N1 > 0 && r1 >= 0) {
+#pragma unroll
+    for (int j = 0; j < N1; ++j)
+      if (j <= r1) put(r1, j, acc1[j]);
+  }
+  if (N2 > 0 && v == 0) put(0, 0, acc2[0]);
+}
+
+template <typename T, int NB, int VW>
+hipError_t launch_gram_t(const GramArgs& a, hipStream_t s) {
+  constexpr int W = NB <= 9 ? 4 : 8, V = NB <= 9 ? 4 : 16;
+  constexpr size_t smem = sizeof(double) * (2 * kGramStage * 16 * NB + 2 * 16 * (NB - 1));
+  auto kern = gram_kernel<T, NB, VW>;
+  if (smem > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3(a.n_work, V / W), dim3(64 * W), smem, s, a);
+  return hipSuccess;
+}
+
+template <typename T>
+hipError_t launch_gram(const GramArgs& a, hipStream_t s) {
+  if (a.n_work <= 0) return hipSuccess;
+  constexpr int VEC = 16 / sizeof(T);
+  const bool vec = a.E % VEC == 0 && reinterpret_cast<uintptr_t>(a.counters) % 16 == 0;
+  (void)hipGetLastError();  // report only this launch's status
+  hipError_t e;
+  switch (gram_blocks(a.E)) {
+    case 5: e = vec ? launch_gram_t<T, 5, VEC>(a, s) : launch_gram_t<T, 5, 1>(a, s); break;
+    case 9: e = vec ? launch_gram_t<T, 9, VEC>(a, s) : launch_gram_t<T, 9, 1>(a, s); break;
+    default: e = vec ? launch_gram_t<T, 17, VEC>(a, s) : launch_gram_t<T, 17, 1>(a, s); break;
+  }
+  return e != hipSuccess ? e : hipGetLastError();
+}
+template hipError_t launch_gram<float>(const GramArgs&, hipStream_t);
+template hipError_t launch_gram<double>(const GramArgs&, hipStream_t);
+
+// Sums of the chunks' partials per optimisation, in two launches, each in a
+// fixed order.  The first reads every partial once: a thread adds one element
+// of every chunk of its slice to the accumulators of the optimisations in the
+// chunk's mask (16 ids per workgroup; the mask is uniform).  The labels' rows
+// are per chunk (the j-th id of its mask), so row 0 of the label blocks takes
+// the row of the id it is summed for; rows other than that and the ones' are
+// not used.
+constexpr int kReduceIds = 16;
 __global__ void __launch_bounds__(256) gram_reduce_kernel(const double* __restrict__ partial,
-                                                          const int32_t* __restrict__ opt_work_begin,
-                                                          int64_t stride, double* __restrict__ out) {
-  const int o = blockIdx.y;
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= stride) return;
-  const int wb = opt_work_begin[o], we = opt_work_begin[o + 1];
+                                                          const GramWork* __restrict__ work, int n_work, int nb, int D,
+                                                          double* __restrict__ out) {
+  const int64_t stride = (int64_t)nb * (nb + 1) / 2 * 256;
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;   // stride is a multiple of 256
+  const int t = blockIdx.x, G = gridDim.y, g = blockIdx.y, o0 = blockIdx.z * kReduceIds;
+  const int tl = nb * (nb - 1) / 2;                    // first block of the labels' block row
+  const int row = threadIdx.x >> 4, col = threadIdx.x & 15;
+  const bool label = t >= tl && row == 0;
+  // label blocks: element [j][col] of block t; in the diagonal one the ones'
+  // column against label j
+  double acc[kReduceIds];
+#pragma unroll
+  for (int o = 0; o < kReduceIds; ++o) acc[o] = 0.0;
+#pragma unroll 2
+  for (int q = g; q < n_work; q += G) {
+    const uint64_t mask = work[q].mask >> o0;
+    const uint64_t below = work[q].mask & ((1ull << o0) - 1ull);
+    const double* p = partial + q * stride;
+    const double v = p[i];
+#pragma unroll
+    for (int o = 0; o < kReduceIds; ++o)
+      if ((mask >> o) & 1ull) {
+        const int j = __popcll(below) + __popcll(mask & ((1ull << o) - 1ull));
+        acc[o] += label ? p[(int64_t)t * 256 + j * 16 + col] : v;
+      }
+  }
+#pragma unroll
+  for (int o = 0; o < kReduceIds; ++o)
+    if (o0 + o < D) out[((int64_t)g * D + o0 + o) * stride + i] = acc[o];
+}
+
+__global__ void __launch_bounds__(256) gram_reduce2_kernel(const double* __restrict__ part, int G, int64_t n,
+                                                           double* __restrict__ out) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;   // n is a multiple of 256
   double v = 0.0;
-  for (int q = wb; q < we; ++q) v += partial[(int64_t)q * stride + i];
-  out[(int64_t)o * stride + i] = v;
+#pragma unroll 4
+  for (int g = 0; g < G; ++g) v += part[g * n + i];
+  out[i] = v;
+}
+
+// Slices of the first launch: about 16 chunks each, so that 45 blocks of
+// elements (128 events) times the slices fill the chip.
+int gram_slices(int n_work) { return std::max(1, std::min(32, n_work / 16)); }
+
+hipError_t launch_gram_reduce(const GramArgs& a, int D, double* slices, double* reduced, hipStream_t s) {
+  if (D <= 0) return hipSuccess;
+  const int nb = gram_blocks(a.E), G = gram_slices(a.n_work);
+  const int64_t stride = gram_stride(a.E);
+  (void)hipGetLastError();  // report only this launch's status
+  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(stride / 256), G, (D + kReduceIds - 1) / kReduceIds), dim3(256),
+                     0, s, a.partial, a.work, a.n_work, nb, D, slices);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(gram_reduce2_kernel, dim3((unsigned)(stride * D / 256)), dim3(256), 0, s, slices, G, stride * D,
+                     reduced);
+  return hipGetLastError();
 }
 
 constexpr int kSolveThreads = 256;
@@ -165,8 +336,15 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
   const int o = blockIdx.x;
   const int E = a.E, n1 = E + 1;
   const int tid = threadIdx.x;
-  const int wb = a.opt_work_begin[o], we = a.opt_work_begin[o + 1];
-  if (wb == we) {
+  const int nb = a.nb;
+  const double* G = a.reduced + (int64_t)o * (nb * (nb + 1) / 2 * 256);   // this optimisation's summed partials
+  const auto at = [&](int i, int j) -> double {   // element of the blocked lower triangle, i >= j
+    const int bi = i >> 4, bj = j >> 4;
+    return G[(bi * (bi + 1) / 2 + bj) * 256 + (i & 15) * 16 + (j & 15)];
+  };
+  const int one = 16 * (nb - 1) + kGramOnes, lab = 16 * (nb - 1);   // rows of the ones and of this label
+  const double count = at(one, one);
+  if (count == 0.0) {
     for (int j = tid; j < n1; j += kSolveThreads) {
       a.W64[(int64_t)o * n1 + j] = __builtin_nan("");
       a.W32[(int64_t)o * w32_ld(E) + j] = 0.0f;
@@ -175,21 +353,14 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
   }
   double* A = use_lds ? reinterpret_cast<double*>(smem) : a.A + (int64_t)o * n1 * n1;
   __shared__ double y[SUGG_MAX_EVENTS + 1];
-  const int64_t stride = (int64_t)E * E + 2 * E + 2;
-  const double* G = a.reduced + (int64_t)o * stride;   // this optimisation's summed partial
   for (int idx = tid; idx < n1 * n1; idx += kSolveThreads) {
     const int i = idx / n1, j = idx - i * n1;
-    int64_t off;
-    if (i < E && j < E) off = i >= j ? (int64_t)i * E + j : (int64_t)j * E + i;   // lower triangle
-    else if (i < E) off = (int64_t)E * E + i;          // column sums
-    else if (j < E) off = (int64_t)E * E + j;
-    else off = (int64_t)E * E + 2 * E + 1;             // sample count
-    double v = G[off];
+    const int hi = i >= j ? i : j, lo = i >= j ? j : i;
+    double v = lo == E ? count : hi == E ? at(one, lo) : at(hi, lo);   // index E: the intercept
     if (i == j && i < E) v += a.lambda;
     A[idx] = v;
   }
-  for (int i = tid; i < n1; i += kSolveThreads)
-    y[i] = G[i < E ? (int64_t)E * E + E + i : (int64_t)E * E + 2 * E];
+  for (int i = tid; i < n1; i += kSolveThreads) y[i] = i < E ? at(lab, i) : G[(nb * (nb + 1) / 2 - 1) * 256 + kGramOnes];   // sum of the labels
   __syncthreads();
   // A = L L^T, lower triangle in place (right-looking).  Every thread reads
   // the pivot itself, so a step needs two barriers; the trailing update uses a
@@ -245,12 +416,7 @@ hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
-  const int64_t stride = (int64_t)a.E * a.E + 2 * a.E + 2;
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)((stride + 255) / 256), a.D), dim3(256), 0, s, a.partial,
-                     a.opt_work_begin, stride, a.reduced);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(solve_kernel, dim3(a.D), dim3(kSolveThreads), smem, s, a, use_lds);
   return hipGetLastError();
 }

@@ -202,38 +202,61 @@ hipError_t launch_zfeat64(const T* counters, const T* cycles, int64_t N, int32_t
                           const double* mu64, const double* sig64, double* z64, double* lcyc64,
                           hipStream_t s);
 
-// One chunk of one optimisation's training pairs.
+// A run of before versions of the same optimisations (see launch_gram_rows).
+struct GramSeg {
+  int64_t base;    // first entry of the row list
+  int32_t first;   // classes: first kernel in the kernel list; pairs: the kernel
+  int32_t sel;     // classes: the version; pairs: the local bit of the optimisation
+  uint64_t bits;   // four bits per optimisation of the class, ascending id: its local bit
+};
+// A before version: its row, and the local bits of the optimisations it is a
+// before version of (after version of the j-th: row + 2^bit).
+struct alignas(16) GramRow {
+  int64_t row;
+  uint64_t bits;
+};
+// The row list of the segments: entry q of a segment is version `sel` of
+// kernel klist[first + q] (classes: kernels with the same optimisations), or
+// the q-th version without bit `sel` of kernel `first` (pairs).
+hipError_t launch_gram_rows(const GramSeg* segs, int nseg, int64_t n, bool pairs, const int32_t* klist,
+                            const int64_t* row_off, GramRow* out, hipStream_t s);
+
+// One chunk of rows that are before versions of the ids in mask.
 struct GramWork {
-  int32_t opt;
-  int32_t list_begin;   // into the per-optimisation (kernel, bit) list
-  int32_t list_end;
+  int64_t begin;   // into the row list
+  uint64_t mask;   // global ids
+  int32_t n;
   int32_t pad;
-  int64_t s_begin;      // sample range within the optimisation's pair space
-  int64_t s_end;
 };
 
 struct GramArgs {
-  const double* z64;        // [N, E]
-  const double* lcyc64;     // [N]
+  const void* counters;     // [N, E], plan dtype
+  const double* lcyc;       // [N] ln(cycles)
+  const double* mu;         // [E]
+  const double* sig;        // [E]
   int32_t E;
+  const GramRow* rows;
   const GramWork* work;
   int32_t n_work;
-  const int64_t* pair_base; // [list] first pair index of each (kernel, bit) entry
-  const int64_t* pair_row0; // [list] row_off of the kernel
-  const int32_t* pair_bit;  // [list] local bit
-  double* partial;          // [n_work, E*E + 2E + 2]
+  double* partial;          // [n_work, gram_stride(E)] lower triangle of 16 x 16 blocks
 };
 
+int gram_blocks(int E);       // block columns: E padded, and the labels' and ones' block
+int64_t gram_stride(int E);   // doubles of one lower triangle
+int gram_slices(int n_work);  // slices of the chunks' sums
+template <typename T>
 hipError_t launch_gram(const GramArgs& a, hipStream_t s);
+// sums of the chunks' partials per id into reduced [D, gram_stride] (the
+// label row 0 holds the id's); slices: [gram_slices, D, gram_stride]
+hipError_t launch_gram_reduce(const GramArgs& a, int D, double* slices, double* reduced, hipStream_t s);
 
-// Sum the chunks of every optimisation (work items sorted by opt) and solve.
+// Solve every optimisation's normal equations.
 struct SolveArgs {
-  const double* partial;
-  const int32_t* opt_work_begin;  // [D+1] range of work items per optimisation
   int32_t E;
   int32_t D;
+  int32_t nb;             // gram_blocks(E)
   double lambda;
-  double* reduced;    // [D, E*E + 2E + 2] workspace: summed partials
+  const double* reduced;  // [D, gram_stride(E)]
   double* A;          // [D, (E+1)^2] workspace when the system does not fit in LDS
   double* W64;        // [D, E+1]
   float* W32;         // [D, w32_ld(E)]

@@ -81,16 +81,13 @@ struct sugg_plan {
   int stat_chunks = 1;
   // fit workspace (allocated on the first fit)
   bool fit_ready = false;
-  double* d_z64 = nullptr;
   double* d_lcyc64 = nullptr;
   double* d_gram_partial = nullptr;
+  double* d_gram_slices = nullptr;
   double* d_solveA = nullptr;
   double* d_reduced = nullptr;
   sugg::GramWork* d_gwork = nullptr;
-  int64_t* d_pair_base = nullptr;
-  int64_t* d_pair_row0 = nullptr;
-  int32_t* d_pair_bit = nullptr;
-  int32_t* d_opt_work_begin = nullptr;
+  sugg::GramRow* d_grows = nullptr;
   int n_gwork = 0;
   // instance-based (IBK) scoring workspace, built on its first use
   IbkPlan* ibk = nullptr;
@@ -102,8 +99,8 @@ struct sugg_plan {
     ibk_plan_free(ibk);
     m5p_plan_free(m5p);
     dfree(d_items); dfree(d_recs); dfree(d_row_off); dfree(d_opt_off); dfree(d_opt_ids); dfree(d_nopts);
-    dfree(d_queue); dfree(d_arrivals); dfree(d_split_edges); dfree(d_chunks); dfree(d_crec); dfree(d_stat_partial); dfree(d_z64); dfree(d_lcyc64); dfree(d_gram_partial);
-    dfree(d_solveA); dfree(d_reduced); dfree(d_gwork); dfree(d_pair_base); dfree(d_pair_row0); dfree(d_pair_bit);
-    dfree(d_opt_work_begin);
+    dfree(d_queue); dfree(d_arrivals); dfree(d_split_edges); dfree(d_chunks); dfree(d_crec); dfree(d_stat_partial);
+    dfree(d_lcyc64); dfree(d_gram_partial); dfree(d_gram_slices); dfree(d_solveA); dfree(d_reduced); dfree(d_gwork);
+    dfree(d_grows);
   }
 };
