@@ -338,8 +338,7 @@ int prepare_fit(sugg_ctx* ctx, sugg_plan* p, hipStream_t s) {
   A(p->d_gram_slices, sizeof(double) * stride * D * gram_slices((int)work.size()));
   A(p->d_reduced, sizeof(double) * stride * D);
   A(p->d_grows, sizeof(GramRow) * g.n);
-  if (sizeof(double) * (size_t)(E + 1) * (E + 1) > 150 * 1024)
-    A(p->d_solveA, sizeof(double) * (size_t)(E + 1) * (E + 1) * std::max(1, D));
+  if (solve_workspace(E)) A(p->d_solveA, sizeof(double) * solve_workspace(E) * std::max(1, D));
   if (e == hipSuccess && !p->d_gwork) e = upload(p->d_gwork, work.data(), sizeof(GramWork) * work.size());
   if (e == hipSuccess) e = upload(d_segs, g.segs.data(), sizeof(GramSeg) * g.segs.size());
   if (e == hipSuccess) e = upload(d_klist, g.klist.data(), sizeof(int32_t) * g.klist.size());

@@ -328,14 +328,53 @@ hipError_t launch_gram_reduce(const GramArgs& a, int D, double* slices, double* 
   return hipGetLastError();
 }
 
-constexpr int kSolveThreads = 256;
+// ---- the solve -----------------------------------------------------------------
+// Lower triangle of 16 x 16 blocks (rows padded to 17 doubles, so that a
+// column of a block spreads over the banks) of the system with its right-hand
+// side as one more row: the features, the intercept (index E), the labels
+// (index E + 1), then the identity.  The factorisation then leaves the forward
+// solution in the labels' row.
+constexpr int kSolveThreads = 512;
+constexpr int kBlkLd = 17, kBlkSz = 16 * kBlkLd;
 constexpr size_t kSolveLdsMax = 150 * 1024;
+static int solve_blocks(int E) { return (E + 2 + 15) / 16; }
+static size_t solve_matrix(int E) { return (size_t)solve_blocks(E) * (solve_blocks(E) + 1) / 2 * kBlkSz; }
+static bool solve_in_lds(int E) { return sizeof(double) * (solve_matrix(E) + 32 * solve_blocks(E)) <= kSolveLdsMax; }
+size_t solve_workspace(int E) { return solve_in_lds(E) ? 0 : solve_matrix(E); }
 
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// g = sqrt(d) and ih = 1 / sqrt(d), d > 0: Goldschmidt's iteration from the
+// hardware's reciprocal square root, and one residual step for the root.
+__device__ __forceinline__ void root_and_inverse(double d, double& g, double& ih) {
+  const double y = __builtin_amdgcn_rsq(d);
+  double h = 0.5 * y;
+  g = d * y;
+  double r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  r = fma(-h, g, 0.5);
+  g = fma(g, r, g);
+  h = fma(h, r, h);
+  g = fma(fma(-g, g, d), h, g);
+  ih = 2.0 * h;
+}
+
+// A = L L^T by block columns: one wave factorises the diagonal block in
+// registers (a row per lane, pivots and multipliers by lane reads), a thread
+// per row solves for the blocks below it, and the matrix cores update the
+// rest.  Then L^T w = t, block by block from the last.
+// A serial chain of E + 1 pivots bounds it: one column at a time, with three
+// barriers each and two more per column and triangular solve, took 288 us at
+// E = 128; now 84 us.
 __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a, const int use_lds) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int o = blockIdx.x;
-  const int E = a.E, n1 = E + 1;
-  const int tid = threadIdx.x;
+  const int E = a.E, n1 = E + 1, M = (E + 2 + 15) / 16;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, l4 = lane >> 4;
   const int nb = a.nb;
   const double* G = a.reduced + (int64_t)o * (nb * (nb + 1) / 2 * 256);   // this optimisation's summed partials
   const auto at = [&](int i, int j) -> double {   // element of the blocked lower triangle, i >= j
@@ -351,52 +390,118 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
     }
     return;
   }
-  double* A = use_lds ? reinterpret_cast<double*>(smem) : a.A + (int64_t)o * n1 * n1;
-  __shared__ double y[SUGG_MAX_EVENTS + 1];
-  for (int idx = tid; idx < n1 * n1; idx += kSolveThreads) {
-    const int i = idx / n1, j = idx - i * n1;
-    const int hi = i >= j ? i : j, lo = i >= j ? j : i;
-    double v = lo == E ? count : hi == E ? at(one, lo) : at(hi, lo);   // index E: the intercept
-    if (i == j && i < E) v += a.lambda;
-    A[idx] = v;
+  double* y = reinterpret_cast<double*>(smem);   // [16 M] the labels' row, then the solution
+  double* inv = y + 16 * M;                      // [16 M] 1 / diagonal of L
+  double* A = use_lds ? inv + 16 * M : a.A + (size_t)o * (M * (M + 1) / 2 * kBlkSz);
+  const auto blk = [&](int bi, int bj) -> double* { return A + (bi * (bi + 1) / 2 + bj) * kBlkSz; };
+  for (int idx = tid, bi = 0, bj = 0, t = 0; idx < M * (M + 1) / 2 * 256; idx += kSolveThreads) {
+    for (; t < (idx >> 8); ++t)   // block t of the lower triangle, row by row
+      if (++bj > bi) {
+        bj = 0;
+        ++bi;
+      }
+    const int r = (idx >> 4) & 15, c = idx & 15, i = bi * 16 + r, j = bj * 16 + c;
+    double v = i == j ? 1.0 : 0.0;
+    if (j <= i && j <= E) {
+      if (i < E) v = at(i, j) + (i == j ? a.lambda : 0.0);
+      else if (i == E) v = j < E ? at(one, j) : count;
+      else if (i == E + 1) v = j < E ? at(lab, j) : G[(nb * (nb + 1) / 2 - 1) * 256 + kGramOnes];   // sum of the labels
+    }
+    A[(idx >> 8) * kBlkSz + r * kBlkLd + c] = v;
   }
-  for (int i = tid; i < n1; i += kSolveThreads) y[i] = i < E ? at(lab, i) : G[(nb * (nb + 1) / 2 - 1) * 256 + kGramOnes];   // sum of the labels
   __syncthreads();
-  // A = L L^T, lower triangle in place (right-looking).  Every thread reads
-  // the pivot itself, so a step needs two barriers; the trailing update uses a
-  // 16 x 16 thread tile over the lower triangle.
   bool bad = false;
-  const int ty = tid >> 4, tx = tid & 15;
-  for (int k = 0; k < n1; ++k) {
-    double d = A[k * n1 + k];
-    if (!(d > 0.0)) {
-      bad = true;
-      d = 1.0;
+  for (int p = 0; p < M; ++p) {
+    if (wave == 0) {
+      double* D = blk(p, p);
+      double row[16], iv = 1.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) row[k] = D[l16 * kBlkLd + k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        if (16 * p + k <= E) {   // the labels' row and the padding have no pivot
+          double d = lane_value(row[k], k);
+          if (!(d > 0.0)) {
+            bad = true;
+            d = 1.0;
+          }
+          double piv, ip;
+          root_and_inverse(d, piv, ip);
+          row[k] = l16 == k ? piv : row[k] * ip;
+          iv = l16 == k ? ip : iv;
+#pragma unroll
+          for (int j = k + 1; j < 16; ++j) row[j] = fma(-row[k], lane_value(row[k], j), row[j]);
+        }
+      }
+      if (lane < 16) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) D[l16 * kBlkLd + k] = row[k];   // above the diagonal: not used
+        inv[16 * p + l16] = iv;
+      }
     }
-    const double piv = sqrt(d);
     __syncthreads();
-    if (tid == 0) A[k * n1 + k] = piv;
-    for (int i = k + 1 + tid; i < n1; i += kSolveThreads) A[i * n1 + k] /= piv;
+    if (16 * p > E) break;
+    for (int i = 16 * (p + 1) + tid; i < 16 * M; i += kSolveThreads) {
+      const double* D = blk(p, p);
+      double* X = blk(i >> 4, p) + (i & 15) * kBlkLd;
+      double x[16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) x[k] = X[k];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        x[k] *= inv[16 * p + k];
+#pragma unroll
+        for (int j = k + 1; j < 16; ++j) x[j] = fma(-x[k], D[j * kBlkLd + k], x[j]);
+      }
+#pragma unroll
+      for (int k = 0; k < 16; ++k) X[k] = x[k];
+    }
     __syncthreads();
-    for (int i = k + 1 + ty; i < n1; i += 16) {
-      const double aik = A[i * n1 + k];
-      for (int j = k + 1 + tx; j <= i; j += 16) A[i * n1 + j] -= aik * A[j * n1 + k];
+    int t = 0;
+    for (int bi = p + 1; bi < M; ++bi) {
+      const double* Li = blk(bi, p) + l16 * kBlkLd + l4;
+      for (int bj = p + 1; bj <= bi; ++bj, ++t) {
+        if (t % (kSolveThreads / 64) != wave) continue;
+        const double* Lj = blk(bj, p) + l16 * kBlkLd + l4;
+        double* C = blk(bi, bj) + l4 * kBlkLd + l16;
+        doublex4 c;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = C[4 * i * kBlkLd];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-Li[4 * k], Lj[4 * k], c, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) C[4 * i * kBlkLd] = c[i];
+      }
     }
     __syncthreads();
   }
-  // L t = rhs, then L^T w = t (column-oriented, one barrier per step)
-  for (int k = 0; k < n1; ++k) {
-    const double yk = y[k] / A[k * n1 + k];
+  for (int j = tid; j < 16 * M; j += kSolveThreads)
+    y[j] = j <= E ? blk((E + 1) >> 4, j >> 4)[((E + 1) & 15) * kBlkLd + (j & 15)] : 0.0;
+  __syncthreads();
+  for (int p = E >> 4; p >= 0; --p) {
+    if (wave == 0) {
+      const double* D = blk(p, p);
+      double col[16], t = y[16 * p + l16];
+      const double iv = inv[16 * p + l16];
+#pragma unroll
+      for (int k = 0; k < 16; ++k) col[k] = D[k * kBlkLd + l16];
+#pragma unroll
+      for (int k = 15; k >= 0; --k)
+        if (16 * p + k <= E) {
+          const double wk = lane_value(t * iv, k);
+          t = l16 == k ? wk : l16 < k ? fma(-col[k], wk, t) : t;
+        }
+      if (lane < 16) y[16 * p + l16] = t;
+    }
     __syncthreads();
-    if (tid == 0) y[k] = yk;
-    for (int i = k + 1 + tid; i < n1; i += kSolveThreads) y[i] -= A[i * n1 + k] * yk;
-    __syncthreads();
-  }
-  for (int k = n1 - 1; k >= 0; --k) {
-    const double yk = y[k] / A[k * n1 + k];
-    __syncthreads();
-    if (tid == 0) y[k] = yk;
-    for (int i = tid; i < k; i += kSolveThreads) y[i] -= A[k * n1 + i] * yk;
+    for (int j = tid; j < 16 * p; j += kSolveThreads) {
+      const double* L = blk(p, j >> 4) + (j & 15);
+      double v = y[j];
+#pragma unroll
+      for (int k = 0; k < 16; ++k)
+        if (16 * p + k <= E) v = fma(-L[k * kBlkLd], y[16 * p + k], v);
+      y[j] = v;
+    }
     __syncthreads();
   }
   for (int j = tid; j < n1; j += kSolveThreads) {
@@ -408,9 +513,8 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
 
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s) {
   if (a.D <= 0) return hipSuccess;
-  const size_t need = sizeof(double) * (size_t)(a.E + 1) * (a.E + 1);
-  const int use_lds = need <= kSolveLdsMax ? 1 : 0;
-  const size_t smem = use_lds ? need : 0;
+  const int use_lds = solve_in_lds(a.E) ? 1 : 0;
+  const size_t smem = sizeof(double) * (32 * solve_blocks(a.E) + (use_lds ? solve_matrix(a.E) : 0));
   if (smem > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(solve_kernel),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);

@@ -257,12 +257,13 @@ struct SolveArgs {
   int32_t nb;             // gram_blocks(E)
   double lambda;
   const double* reduced;  // [D, gram_stride(E)]
-  double* A;          // [D, (E+1)^2] workspace when the system does not fit in LDS
+  double* A;          // [D, solve_workspace(E)] when the system does not fit in LDS
   double* W64;        // [D, E+1]
   float* W32;         // [D, w32_ld(E)]
   int32_t* status;
 };
 
+size_t solve_workspace(int E);   // doubles per optimisation (0: LDS)
 hipError_t launch_solve(const SolveArgs& a, hipStream_t s);
 
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
