@@ -11,10 +11,11 @@
 namespace sugg {
 
 constexpr int kIbkMaxK = 16;       // largest k
-constexpr int kIbkList = 24;       // FP32 candidates kept per query (k plus a margin, at most 24)
-constexpr int kIbkQueries = 128;   // queries per workgroup (4 waves x 32)
+constexpr int kIbkQueries = 256;   // queries per workgroup (4 waves x 64)
 constexpr int kIbkTile = 32;       // database samples per staged tile
-constexpr int kIbkQueue = 30;      // queued candidates per lane (at least 16, one tile's)
+constexpr int kIbkQueue = 23;      // queued candidates per lane (above 16, half a tile's; 78 KB of LDS at 128 events)
+
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 // Database of one fitted IBK model.  Samples of global optimisation o are
 // [off[o], off[o+1]), stored kernel by kernel, then by before-version S; each
@@ -22,12 +23,16 @@ constexpr int kIbkQueue = 30;      // queued candidates per lane (at least 16, o
 struct IbkModel {
   int E = 0, Epad = 0, D = 0, k = 10;
   int64_t Ntr = 0, Ns = 0;
-  float* Z = nullptr;          // [Ns, Epad] FP32 sample vectors, columns >= E zero
+  halfx8* Zt = nullptr;        // sample vectors in tiles of 32 per id, split into FP16 halves in
+                               //   matrix-core order (ibk_pack_kernel), scaled by 1 / inv_scale
+  float inv_scale = 1.0f;      // power of two
   double* Z64 = nullptr;       // [Ntr, E] FP64 standardised training rows (exact distances)
   int32_t* srow = nullptr;     // [Ns] training row of each sample (its before version)
   double dt_norm = 0.0;        // Euclidean norm over columns of max_rows |Z32 - Z64|: the
                                //   FP32 rounding of any stored vector is at most this
-  float* norm = nullptr;       // [Ns] their squared norms
+  float* norm = nullptr;       // [tiles * 32] their squared norms, infinite for the fill of a last tile
+  int32_t* d_toff = nullptr;   // [D+1] first tile of each id
+  int32_t* sidx = nullptr;     // [tiles * 32] the sample (within its id) in each slot, -1: fill
   double* y = nullptr;         // [Ns] ln cyc(before) - ln cyc(after)
   int64_t* d_off = nullptr;    // [D+1]
   double* mu64 = nullptr;      // [E] training column means of ln(c / cyc)
@@ -57,8 +62,7 @@ struct IbkPlan {
   int Epad = 0;
   float* zq = nullptr;         // [N, Epad] standardised rows of the batch
   void* edges = nullptr;       // [N] plan dtype: chain-edge predictions
-  float* part_d = nullptr;     // candidate lists of every query (per sample share when split)
-  int32_t* part_i = nullptr;
+  double* part = nullptr;      // candidate lists of every query (per sample share when split)
   int64_t part_cap = 0;        // entries allocated
   int32_t* exact_q = nullptr;  // queries whose FP32 candidates could not be certified, and
   int32_t* exact_n = nullptr;  //   their count (device), searched again in FP64
@@ -69,8 +73,11 @@ struct IbkPlan {
 
 struct IbkKnnArgs {
   const float* zq;
-  const float* Z;
+  const halfx8* Zt;
   const float* norm;
+  const int32_t* toff;
+  const int32_t* sidx;
+  float inv_scale;
   const double* y;
   const int64_t* off;
   const int32_t* q_src;
@@ -78,10 +85,9 @@ struct IbkKnnArgs {
   const int32_t* tiles;
   int32_t Epad;
   int32_t k;
-  int32_t kt;                  // FP32 candidates kept per query (k plus a margin)
+  int32_t kt;                  // candidates kept per query (k plus a margin)
   int32_t split;               // sample partitions per query tile (workgroups per tile)
-  float* part_d;               // [queries, split, kIbkList] candidate lists
-  int32_t* part_i;
+  double* part;                // [split, kt, queries] candidate lists (keys)
   int64_t n_queries;
   int32_t n_tiles;
   void* out;                   // plan dtype
@@ -101,26 +107,29 @@ struct IbkKnnArgs {
 
 template <typename T>
 hipError_t launch_ibk_z(const T* counters, const T* cycles, int64_t N, int32_t E, int32_t Epad,
-                        const double* mu, const double* sig, float* z, int32_t* status, hipStream_t s);
+                        const double* mu, const double* sig, float* z, int32_t* status, int32_t* zero,
+                        hipStream_t s);
 template <typename T>
 hipError_t launch_ibk_nan(T* p, int64_t n, hipStream_t s);
-hipError_t launch_ibk_norm(const float* z, int64_t N, int32_t Epad, float* norm, hipStream_t s);
-hipError_t launch_ibk_gather(const float* Z, const int32_t* srow, int64_t Ns, int32_t Epad, float* Zs,
-                             hipStream_t s);
+// the samples' vectors (rows srow of Z) and norms in tiles (see IbkModel)
+hipError_t launch_ibk_pack(const float* Z, const int32_t* srow, const int64_t* off, const int32_t* toff,
+                           const int32_t* step, int32_t D, int64_t n_tiles, int32_t Epad, float scale, halfx8* Zt,
+                           float* norm, int32_t* sidx, hipStream_t s);
 template <typename T>
 hipError_t launch_ibk_labels(const T* cycles, const int32_t* before, const int32_t* after, int64_t Ns,
                              double* y, hipStream_t s);
-// per column, the largest |z32 - z64| over the rows (as float bits, maxed into out[E])
+// per column, the largest |z32 - z64| over the rows, and in out[E] the largest
+// finite |z32| (float bits, maxed into out[E + 1])
 hipError_t launch_ibk_dz(const float* z32, int32_t Epad, const double* z64, int64_t N, int32_t E, uint32_t* out,
                          hipStream_t s);
-// FP32 candidate search, re-ranking of the candidates by FP64 distance with a
+// candidate search, re-ranking of the candidates by FP64 distance with a
 // certificate, and an FP64 search over every sample for the queries the
 // certificate does not cover; writes the mean label of the k nearest
 template <typename T>
 hipError_t launch_ibk_knn(const IbkKnnArgs& a, int n_tiles, hipStream_t s);
 // candidates kept per query for a given k
 inline int ibk_kt(int k) { return k <= 4 ? 8 : k <= 10 ? 16 : 24; }
-int ibk_split(int Epad, int k, int n_tiles, int cus);
+int ibk_split(int64_t max_samples, int n_tiles, int cus);
 // Composition and top-n from chain edges (dtype TE, the composition's
 // arithmetic) or from a grid (dtype TO); outputs of dtype TO.
 template <typename TE, typename TO>

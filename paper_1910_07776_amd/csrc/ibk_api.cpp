@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <numeric>
 #include <vector>
 
 #include "ibk.hpp"
@@ -17,7 +18,7 @@ using namespace sugg;
 
 void ibk_model_free(IbkModel*& m) {
   if (!m) return;
-  dfree(m->Z); dfree(m->Z64); dfree(m->srow); dfree(m->norm); dfree(m->y); dfree(m->d_off);
+  dfree(m->Zt); dfree(m->d_toff); dfree(m->sidx); dfree(m->Z64); dfree(m->srow); dfree(m->norm); dfree(m->y); dfree(m->d_off);
   dfree(m->mu64); dfree(m->sig64); dfree(m->mu_t); dfree(m->isg_t);
   delete m;
   m = nullptr;
@@ -27,8 +28,7 @@ void ibk_plan_free(IbkPlan*& p) {
   if (!p) return;
   dfree(p->zq);
   dfree(p->edges);
-  dfree(p->part_d);
-  dfree(p->part_i);
+  dfree(p->part);
   dfree(p->exact_q);
   dfree(p->exact_n);
   for (auto& q : p->q) {
@@ -87,45 +87,58 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
     hb.insert(hb.end(), bef[o].begin(), bef[o].end());
     ha.insert(ha.end(), aft[o].begin(), aft[o].end());
   }
-  int32_t* d_after = nullptr;
+  int32_t *d_after = nullptr, *d_step = nullptr;
   double* partial = nullptr;
   float* zrows = nullptr;
   const int chunks = colstats_chunks(std::max<int64_t>(p->N, 1));
   const int64_t ns1 = std::max<int64_t>(m->Ns, 1);
+  std::vector<int32_t> toff(p->D + 1, 0);
+  for (int o = 0; o < p->D; ++o)
+    toff[o + 1] = toff[o] + (int32_t)((m->off[o + 1] - m->off[o] + kIbkTile - 1) / kIbkTile);
+  // the order of the samples in their tiles (see ibk_pack_kernel)
+  std::vector<int32_t> step(p->D, 1);
+  for (int o = 0; o < p->D; ++o) {
+    const int64_t n = m->off[o + 1] - m->off[o];
+    int64_t q = std::max<int64_t>(1, (int64_t)(0.6180339887498949 * (double)n));
+    while (std::gcd(q, std::max<int64_t>(n, 1)) != 1) ++q;
+    step[o] = (int32_t)q;
+  }
+  const int64_t n_tiles = toff[p->D], slots = std::max<int64_t>(n_tiles, 1) * kIbkTile;
   hipError_t e = hipMalloc((void**)&m->mu64, sizeof(double) * E);
   if (e == hipSuccess) e = hipMalloc((void**)&m->sig64, sizeof(double) * E);
   if (e == hipSuccess) e = hipMalloc((void**)&m->mu_t, sizeof(T) * E);
   if (e == hipSuccess) e = hipMalloc((void**)&m->isg_t, sizeof(T) * E);
   if (e == hipSuccess) e = hipMalloc((void**)&partial, sizeof(double) * 2 * E * chunks);
   if (e == hipSuccess) e = hipMalloc((void**)&zrows, sizeof(float) * (size_t)p->N * m->Epad);
-  if (e == hipSuccess) e = hipMalloc((void**)&m->Z, sizeof(float) * (size_t)ns1 * m->Epad);
-  if (e == hipSuccess) e = hipMalloc((void**)&m->norm, sizeof(float) * (size_t)ns1);
+  if (e == hipSuccess) e = hipMalloc((void**)&m->Zt, 2 * sizeof(_Float16) * (size_t)slots * m->Epad);
+  if (e == hipSuccess) e = hipMalloc((void**)&m->norm, sizeof(float) * (size_t)slots);
+  if (e == hipSuccess) e = hipMalloc((void**)&m->sidx, sizeof(int32_t) * (size_t)slots);
+  if (e == hipSuccess) e = upload_vec(m->d_toff, toff);
+  if (e == hipSuccess) e = upload_vec(d_step, step);
   if (e == hipSuccess) e = upload_vec(m->srow, hb);
   if (e == hipSuccess) e = hipMalloc((void**)&m->Z64, sizeof(double) * (size_t)std::max<int64_t>(p->N, 1) * E);
   if (e == hipSuccess) e = upload_vec(d_after, ha);
   if (e == hipSuccess) e = hipMalloc((void**)&m->y, sizeof(double) * ns1);
   if (e == hipSuccess) e = upload_vec(m->d_off, m->off);
-  // Tier 1 statistics, standardised rows, sample vectors in database order,
-  // their norms, labels
+  // Tier 1 statistics, standardised rows, labels
   if (e == hipSuccess)
     e = launch_colstats<T>(c, cyc, p->N, E, partial, chunks, m->mu64, m->sig64, (T*)m->mu_t, (T*)m->isg_t,
                            ctx->d_status, s);
-  if (e == hipSuccess) e = launch_ibk_z<T>(c, cyc, p->N, E, m->Epad, m->mu64, m->sig64, zrows, ctx->d_status, s);
-  if (e == hipSuccess) e = launch_ibk_gather(zrows, m->srow, m->Ns, m->Epad, m->Z, s);
-  if (e == hipSuccess) e = launch_ibk_norm(m->Z, m->Ns, m->Epad, m->norm, s);
+  if (e == hipSuccess) e = launch_ibk_z<T>(c, cyc, p->N, E, m->Epad, m->mu64, m->sig64, zrows, ctx->d_status, nullptr, s);
   if (e == hipSuccess) e = launch_ibk_labels<T>(cyc, m->srow, d_after, m->Ns, m->y, s);
   // FP64 standardised training rows for exact distances
   double* lcyc = nullptr;
   if (e == hipSuccess) e = hipMalloc((void**)&lcyc, sizeof(double) * (size_t)std::max<int64_t>(p->N, 1));
   if (e == hipSuccess) e = launch_zfeat64<T>(c, cyc, p->N, E, m->mu64, m->sig64, m->Z64, lcyc, s);
-  // the largest FP32 rounding of each column of the stored vectors
+  // the largest FP32 rounding of each column of the stored vectors, and their
+  // largest value
   uint32_t* dz = nullptr;
-  if (e == hipSuccess) e = hipMalloc((void**)&dz, sizeof(uint32_t) * E);
-  if (e == hipSuccess) e = hipMemsetAsync(dz, 0, sizeof(uint32_t) * E, s);
+  if (e == hipSuccess) e = hipMalloc((void**)&dz, sizeof(uint32_t) * (E + 1));
+  if (e == hipSuccess) e = hipMemsetAsync(dz, 0, sizeof(uint32_t) * (E + 1), s);
   if (e == hipSuccess) e = launch_ibk_dz(zrows, m->Epad, m->Z64, p->N, E, dz, s);
-  std::vector<uint32_t> hdz(E, 0);
+  std::vector<uint32_t> hdz(E + 1, 0);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e == hipSuccess) e = hipMemcpy(hdz.data(), dz, sizeof(uint32_t) * E, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemcpy(hdz.data(), dz, sizeof(uint32_t) * (E + 1), hipMemcpyDeviceToHost);
   if (e == hipSuccess) {
     double acc = 0.0;
     for (int j = 0; j < E; ++j) {
@@ -134,10 +147,21 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
       acc += (double)f * (double)f;
     }
     m->dt_norm = std::sqrt(acc) * (1.0 + 1e-12);
+    // the power of two that takes the largest stored value to [2^14, 2^15)
+    float zmax;
+    std::memcpy(&zmax, &hdz[E], sizeof zmax);
+    int x = 0;
+    (void)std::frexp(zmax > 0.0f ? zmax : 1.0f, &x);
+    x = std::min(std::max(x, -85), 115);
+    m->inv_scale = std::ldexp(1.0f, x - 15);
+    e = launch_ibk_pack(zrows, m->srow, m->d_off, m->d_toff, d_step, p->D, n_tiles, m->Epad, std::ldexp(1.0f, 15 - x),
+                        m->Zt, m->norm, m->sidx, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);   // zrows is freed
   }
   dfree(dz);
   dfree(lcyc);
   dfree(d_after);
+  dfree(d_step);
   dfree(partial);
   dfree(zrows);
   if (e != hipSuccess) {
@@ -244,12 +268,25 @@ int score_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, T* grid, T* t
   int rc = build_queries(ctx, p, m, mode);
   if (rc) return rc;
   const IbkQueries& q = w->q[mode];
-  e = launch_ibk_z<T>(c, cyc, p->N, p->E, w->Epad, m->mu64, m->sig64, w->zq, ctx->d_status, s);
+  if (w->exact_cap < std::max<int64_t>(q.n, 1)) {
+    dfree(w->exact_q);
+    dfree(w->exact_n);
+    w->exact_cap = 0;
+    e = hipMalloc((void**)&w->exact_q, sizeof(int32_t) * std::max<int64_t>(q.n, 1));
+    if (e == hipSuccess) e = hipMalloc((void**)&w->exact_n, sizeof(int32_t));
+    if (e == hipSuccess) e = hipMemset(w->exact_n, 0, sizeof(int32_t));
+    if (e == hipSuccess) w->exact_cap = std::max<int64_t>(q.n, 1);
+  }
+  if (e == hipSuccess)
+    e = launch_ibk_z<T>(c, cyc, p->N, p->E, w->Epad, m->mu64, m->sig64, w->zq, ctx->d_status, w->exact_n, s);
   if (e == hipSuccess && grid) e = launch_ibk_nan<T>(grid, p->N * p->Bmax, s);
   IbkKnnArgs a;
   a.zq = w->zq;
-  a.Z = m->Z;
+  a.Zt = m->Zt;
   a.norm = m->norm;
+  a.toff = m->d_toff;
+  a.sidx = m->sidx;
+  a.inv_scale = m->inv_scale;
   a.y = m->y;
   a.off = m->d_off;
   a.q_src = q.src;
@@ -274,27 +311,18 @@ int score_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, T* grid, T* t
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device) != hipSuccess || cus <= 0)
     cus = 256;
-  a.split = ibk_split(w->Epad, m->k, q.n_tiles, cus);
-  const int64_t need = std::max<int64_t>(q.n, 1) * a.split * kIbkList;
+  int64_t max_samples = 0;
+  for (int o = 0; o < p->D; ++o)
+    if (o < m->D && q.per_opt[o] > 0) max_samples = std::max(max_samples, m->off[o + 1] - m->off[o]);
+  a.split = ibk_split(max_samples, q.n_tiles, cus);
+  const int64_t need = std::max<int64_t>(q.n, 1) * a.split * a.kt;
   if (w->part_cap < need) {
-    dfree(w->part_d);
-    dfree(w->part_i);
+    dfree(w->part);
     w->part_cap = 0;
-    if (e == hipSuccess) e = hipMalloc((void**)&w->part_d, sizeof(float) * need);
-    if (e == hipSuccess) e = hipMalloc((void**)&w->part_i, sizeof(int32_t) * need);
+    if (e == hipSuccess) e = hipMalloc((void**)&w->part, sizeof(double) * need);
     if (e == hipSuccess) w->part_cap = need;
   }
-  if (w->exact_cap < std::max<int64_t>(q.n, 1)) {
-    dfree(w->exact_q);
-    dfree(w->exact_n);
-    w->exact_cap = 0;
-    if (e == hipSuccess) e = hipMalloc((void**)&w->exact_q, sizeof(int32_t) * std::max<int64_t>(q.n, 1));
-    if (e == hipSuccess) e = hipMalloc((void**)&w->exact_n, sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(w->exact_n, 0, sizeof(int32_t));
-    if (e == hipSuccess) w->exact_cap = std::max<int64_t>(q.n, 1);
-  }
-  a.part_d = w->part_d;
-  a.part_i = w->part_i;
+  a.part = w->part;
   a.exact_q = w->exact_q;
   a.exact_n = w->exact_n;
   w->exact_mode = mode;
