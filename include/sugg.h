@@ -105,11 +105,14 @@ SUGG_API int32_t sugg_plan_max_opts(const sugg_plan* plan); /* max B_k, or -1 */
  * per workgroup, the last of a kernel's workgroups composing and ranking it
  * (per-plan counters, re-armed by each launch).  unroll = -1, -2 or -4
  * selects the streaming form (1, 2 or 4 rows per lane group and stage):
- * workgroups of 4 waves each take a chunk of consecutive whole kernels in
+ * workgroups of 4 waves (16 or 8, one row per group and stage, where there
+ * are few large chunks) each take a chunk of consecutive whole kernels in
  * memory order (about sugg_plan_get_items rows, any mix of B) and stream,
- * compose and rank it.  The split and streaming forms serve sugg_suggest and
- * sugg_predict without a grid; other calls take the fused form with unroll
- * 1.  Results do not depend on the shape. */
+ * compose and rank it.  The split form serves sugg_suggest and sugg_predict
+ * without a grid, other calls then take the fused form with unroll 1.  A new
+ * plan's shape is chosen from its rows, its largest kernel and E (streaming
+ * chunks then have the largest kernel's size, 64 to 512 rows, until
+ * sugg_plan_set_items).  Results do not depend on the shape. */
 SUGG_API int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int32_t grid);
 SUGG_API int32_t sugg_plan_get_launch(const sugg_plan* plan, int32_t* waves, int32_t* unroll, int32_t* grid);
 

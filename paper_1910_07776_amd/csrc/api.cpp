@@ -81,15 +81,52 @@ void build_items(const std::vector<int32_t>& nopts, const std::vector<int64_t>& 
   }
 }
 
+// Launch shape of a new plan's scoring kernel, from the batch's rows and its
+// largest kernel; chunk: rows of a streaming chunk.
+// - From 65,536 rows, and where a kernel has 128 versions or more, the
+//   streaming form, chunks of the largest kernel's size (64 to 512 rows).  us
+//   per pass, fused shape (4 waves, 2 rows a stage) against this one, 128
+//   FP32 events: 16,384 kernels of 4..10 optimisations 493 / 441, 4096 169 /
+//   113, 256 40 / 22; 64 versions x 8192 95 / 44, x 2048 19.0 / 17.5; 16 x
+//   65,536 162 / 132; 256 x 2048 95 / 46, x 16 16.1 / 12.9; 1024 x 4096 429 /
+//   383.  40 events, 4096 kernels of 4..10 107 / 47; 128 FP64 events, 256 of
+//   4..8 36 / 30.
+// - Smaller batches of smaller kernels: the fused form with 8 waves a
+//   workgroup where a lane holds at most 32 bytes of a row (one or two rows a
+//   stage), else 4 waves: 64 versions x 1 kernel 7.8 against 6.3 us, x 64 7.4
+//   against 6.6, x 512 9.0 against 7.5; 2 kernels of 40 FP64 events 10.0
+//   against 8.6; 256 FP32 events the other way round, 19.0 against 9.9.
+PathLaunch default_launch(int64_t rows, int Bmax, int E, int dtype, int& chunk) {
+  chunk = std::min(std::max(1 << Bmax, 64), 512);
+  if (rows >= 65536 || Bmax >= 7) return PathLaunch{4, -2, 0};
+  const int lane_bytes = (dtype == SUGG_F32 ? 4 : 8) * (E <= 64 ? 4 : E <= 128 ? 8 : 16);
+  if (lane_bytes > 32) return PathLaunch{4, 2, 0};
+  return PathLaunch{8, dtype == SUGG_F32 ? 1 : 2, 0};
+}
+
+// Wide workgroups for the streaming form where its chunks are large and few:
+// a chunk of 1024 rows takes a 4-wave workgroup about 35 us, whatever else
+// runs.  us per pass, 4 waves against 16, 128 FP32 events: 1 kernel of 1024
+// versions 38 / 21, 256 41 / 31, 512 53 / 50, 1024 equal, 4096 387 / 390;
+// 4..10 optimisations, 256 kernels 39 / 22, 1000 41 / 38, 2048 63 / 66; of 256
+// versions, 512 kernels 20 / 25.  The grid of 1000 kernels of 4..10 (100
+// events) 123 / 61.  A masked pass (most chunks end at once) with 1024
+// kernels of 1024 versions 129 / 114 (the whole serving query), 4096 303 / 312.
+bool wide_chunks(const sugg_plan* p, bool masked) {
+  return p->chunk_max_rows >= 512 && p->n_chunks <= (masked ? 8 : 3) * p->cus;
+}
+
 // The plan's work list for items of about `target` rows (build_items), the
-// arithmetic geometry of batches whose kernels all have one B, and the
-// kernel records; replaces a previous list.  Synchronous.
-hipError_t plan_items(sugg_plan* p, int target) {
+// arithmetic geometry of batches whose kernels all have one B, the kernel
+// records, and the chunks of about `chunk` rows; replaces a previous list.
+// Synchronous.
+hipError_t plan_items(sugg_plan* p, int target, int chunk) {
   const int K = p->K;
   std::vector<Item> items;
   std::vector<int32_t> ik;
   build_items(p->nopts, p->row_off, target, items, ik, p->max_item_rows, p->max_item_kernels);
   p->item_rows = target;
+  p->chunk_rows = chunk;
   // a batch whose kernels all have the same B gets arithmetic item geometry
   p->uni_B = -1;
   p->uni_nk = 0;
@@ -122,7 +159,7 @@ hipError_t plan_items(sugg_plan* p, int target) {
     for (int b = 0; b < p->nopts[k]; ++b) r.opt[b] = (uint8_t)p->opt_ids[p->opt_off[k] + b];
   }
   // streaming form: consecutive whole kernels in memory order, a chunk closed
-  // before it would pass `target` rows (a larger kernel is a chunk alone).
+  // before it would pass `chunk` rows (a larger kernel is a chunk alone).
   // The kernels of the last tenth of the rows go into chunks of a quarter of
   // the target, and the chunks are dispatched largest first: the workgroups
   // that start last are then short, and the device stays nearly full until
@@ -133,18 +170,18 @@ hipError_t plan_items(sugg_plan* p, int target) {
   p->chunk_max_rows = 1;
   p->chunk_max_nk = 1;
   const int64_t n_rows = K > 0 ? p->row_off[K] : 0;
-  const int tail_target = std::max(target / 4, 128);
+  const int tail_target = std::max(chunk / 4, 128);
   for (int k = 0; k < K;) {
     Chunk c;
     std::memset(&c, 0, sizeof c);
     c.row0 = p->row_off[k];
     c.k0 = k;
-    const int64_t cap = 10 * c.row0 >= 9 * n_rows ? std::min(target, tail_target) : target;
+    const int64_t cap = 10 * c.row0 >= 9 * n_rows ? std::min(chunk, tail_target) : chunk;
     int64_t rows = 0;
     while (k < K && (c.nk == 0 || rows + ((int64_t)1 << p->nopts[k]) <= cap)) {
       CRec& r = crec[k];
       std::memset(&r, 0, sizeof r);
-      r.rel = (int16_t)rows;   // < max(target, 2^SUGG_MAX_OPTS) <= 4096
+      r.rel = (int16_t)rows;   // < max(chunk, 2^SUGG_MAX_OPTS) <= 4096
       r.B = (int8_t)p->nopts[k];
       for (int b = 0; b < p->nopts[k]; ++b) r.op[b] = (uint8_t)p->opt_ids[p->opt_off[k] + b];
       rows += (int64_t)1 << p->nopts[k];
@@ -464,7 +501,7 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
   a.status = ctx->d_status;
   if (p->cfg.unroll == 0 && p->split_ok() && !grid && !kmask)
     return ctx->hip(launch_path_split<T>(a, p->d_arrivals, (T*)p->d_split_edges, s), "scoring kernel");
-  if (p->cfg.unroll < 0 && !grid && !kmask &&
+  if (p->cfg.unroll < 0 &&
       path_chunk_lds(sizeof(T), ctx->D, p->E, p->chunk_max_rows, p->chunk_max_nk) <= kLdsPerWorkgroup) {
     ChunkArgs<T> ch;
     ch.counters = c;
@@ -480,6 +517,10 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
     ch.n_chunks = p->n_chunks;
     ch.max_rows = p->chunk_max_rows;
     ch.max_nk = p->chunk_max_nk;
+    ch.wide = wide_chunks(p, kmask != nullptr) ? 1 : 0;
+    ch.kmask = kmask;
+    ch.grid = grid;
+    ch.grid_ld = p->Bmax;
     ch.table = table;
     ch.idx_out = idx;
     ch.score_out = score;
@@ -681,11 +722,13 @@ int32_t sugg_plan_create(sugg_ctx* ctx, int32_t K, int32_t E, int32_t D, int32_t
     }
   }
   // item size: enough items to spread over the chip, at most 256 rows packed
-  const int cus = cu_count(ctx->device);
+  const int cus = p->cus = cu_count(ctx->device);
   int target = 256;
   while (target > 64 && p->N / target < 2 * cus) target >>= 1;
   p->stat_chunks = colstats_chunks(std::max<int64_t>(p->N, 1));
-  hipError_t e = plan_items(p, target);
+  int chunk = target;
+  p->cfg = default_launch(p->N, p->Bmax, E, dtype, chunk);
+  hipError_t e = plan_items(p, target, chunk);
   if (e == hipSuccess) e = upload(p->d_row_off, p->row_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_off, p->opt_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_ids, p->opt_ids.data(), sizeof(int32_t) * nid);
@@ -1090,9 +1133,9 @@ int32_t sugg_plan_set_items(sugg_ctx* ctx, sugg_plan* plan, int32_t rows) {
   if (!ctx) return SUGG_E_ARG;
   if (!plan || plan->ctx != ctx) return ctx->fail(SUGG_E_ARG, "plan missing or from another context");
   if (rows < 16 || rows > 4096) return ctx->fail(SUGG_E_ARG, "item rows %d outside [16, 4096]", rows);
-  if (rows == plan->item_rows) return SUGG_OK;
+  if (rows == plan->item_rows && rows == plan->chunk_rows) return SUGG_OK;
   if (!device_ok(ctx)) return ctx->fail(SUGG_E_HIP, "cannot select device");
-  return ctx->hip(plan_items(plan, rows), "plan items");
+  return ctx->hip(plan_items(plan, rows, rows), "plan items");
 }
 
 int32_t sugg_plan_get_items(const sugg_plan* plan) { return plan ? plan->item_rows : -1; }
@@ -1127,7 +1170,10 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
   if (e == hipSuccess) e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
   const PathLaunch keep = plan->cfg;
-  const int keep_items = plan->item_rows;
+  const int keep_items = plan->item_rows, keep_chunk = plan->chunk_rows;
+  const auto set_items = [&](int items, int chunk) -> hipError_t {
+    return plan->item_rows != items || plan->chunk_rows != chunk ? plan_items(plan, items, chunk) : hipSuccess;
+  };
   PathLaunch best = keep;
   int best_items = keep_items;
   float best_ms = 1e30f;
@@ -1163,7 +1209,7 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
   for (int ir : kTuneItems)
     for (const auto& wu : shapes) {
       if (e != hipSuccess) break;
-      if (plan->item_rows != ir) e = plan_items(plan, ir);
+      e = set_items(ir, ir);
       if (e != hipSuccess) break;
       const int u = wu.second;
       plan->cfg = PathLaunch{wu.first, u, 0};
@@ -1183,7 +1229,7 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
     }
   // the split form (equal kernels of at most 64 versions): one more candidate
   if (times_ms) times_ms[ci] = -1.f;
-  if (e == hipSuccess && plan->item_rows != keep_items) e = plan_items(plan, keep_items);
+  if (e == hipSuccess) e = set_items(keep_items, keep_chunk);
   if (e == hipSuccess && plan->split_ok()) {
     plan->cfg = PathLaunch{4, 0, 0};
     float ms = 0.f;
@@ -1199,7 +1245,7 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
   std::vector<float> fin_ms(n_fin, 0.f);
   for (int round = 0; round < 2 && e == hipSuccess; ++round)
     for (size_t f = 0; f < n_fin && e == hipSuccess; ++f) {
-      if (plan->item_rows != cands[f].items) e = plan_items(plan, cands[f].items);
+      e = set_items(cands[f].items, cands[f].items);
       if (e != hipSuccess) break;
       plan->cfg = cands[f].cfg;
       float ms = 0.f;
@@ -1215,11 +1261,8 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
     }
   }
   plan->cfg = e == hipSuccess ? best : keep;
-  const int want_items = e == hipSuccess ? best_items : keep_items;
-  if (plan->item_rows != want_items) {
-    const hipError_t e2 = plan_items(plan, want_items);
-    if (e == hipSuccess) e = e2;
-  }
+  const hipError_t e2 = e == hipSuccess ? set_items(best_items, best_items) : set_items(keep_items, keep_chunk);
+  if (e == hipSuccess) e = e2;
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   (void)hipFree(table);

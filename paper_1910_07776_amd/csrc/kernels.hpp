@@ -138,6 +138,10 @@ struct ChunkArgs {
   int32_t n_chunks;
   int32_t max_rows;          // largest chunk
   int32_t max_nk;            // most kernels in a chunk
+  int32_t wide;              // nonzero: workgroups of 1024 (or 512) threads, one row per lane group and stage
+  const int32_t* kmask;      // [K] or null: only kernels with kmask != 0 are scored and written
+  T* grid;                   // [N, grid_ld] or null (then no ranking)
+  int32_t grid_ld;
   T* table;                  // nullable
   int32_t* idx_out;          // nullable (then no ranking)
   T* score_out;

@@ -20,7 +20,22 @@
 
 namespace sugg {
 
+// Threads per workgroup: 256, or the wide form's 1024 (512 where a lane holds
+// more than 32 bytes of a row, for its registers), which ends a large chunk
+// sooner where there are too few chunks to fill the chip.
 constexpr int kChunkThreads = 256;
+template <typename T, int VPL>
+constexpr int chunk_wide() { return sizeof(T) * VPL <= 32 ? 1024 : 512; }
+
+// Lane 0's value of the row of 16 lanes, in every lane.
+__device__ __forceinline__ float row_first(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150, 0xF, 0xF, false));
+}
+__device__ __forceinline__ double row_first(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
 
 struct ChunkSmem {
   int ep;
@@ -66,13 +81,18 @@ __device__ __forceinline__ VecN<T, 16 / sizeof(T)> weight_vec(const T* W, int ld
   return r;
 }
 
-template <typename T, int VPL, int VW, int U, int KT, bool FULL>
-__global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkArgs<T> a) {
+// GRID: every optimisation a version lacks is predicted and the grid written
+// (no ranking).  With kmask, chunks without a selected kernel end at once and
+// only selected kernels' rows are used and their outputs written.
+template <typename T, int VPL, int VW, int U, int KT, bool FULL, int TH, bool GRID>
+__global__ void __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(
+    TH == 1024 && sizeof(T) == 4 ? 8 : 1)))   // two wide FP32 workgroups per compute unit
+path_chunk_kernel(const ChunkArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NCH = VPL / VW;
   constexpr int VEC = 16 / sizeof(T);
-  constexpr int kGroups = kChunkThreads / kRowLanes;
-  constexpr int kWaves = kChunkThreads / kWave;
+  constexpr int kGroups = TH / kRowLanes;
+  constexpr int kWaves = TH / kWave;
   const int E = a.E, D = a.D;
   const int tid = threadIdx.x, g = tid / kRowLanes, l16 = tid % kRowLanes, lane = tid % kWave, wave = tid / kWave;
   const ChunkSmem ly = chunk_smem<T>(D, E, a.max_rows, a.max_nk);
@@ -116,6 +136,11 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
   int4* krv = reinterpret_cast<int4*>(kr);
   const Chunk ck = a.chunks[blockIdx.x];
   const int R = ck.R, nk = ck.nk;
+  if (a.kmask) {   // uniform
+    int sel = 0;
+    for (int j = tid; j < nk; j += TH) sel |= a.kmask[ck.k0 + j];
+    if (!__syncthreads_or(sel)) return;
+  }
   // loads in issue order: this chunk's kernel records and the model (small,
   // needed first), then the first two steps of rows; whatever would wait on
   // a load (a loop over a larger model or many kernels) comes before the rows
@@ -124,13 +149,13 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
   const int nwv = D * (EP / VEC);
   VecN<T, VEC> wv0, wv1;
   if (tid < nwv) wv0 = weight_vec<T, FULL>(a.W, a.ldw, E, EP, tid);
-  if (tid + kChunkThreads < nwv) wv1 = weight_vec<T, FULL>(a.W, a.ldw, E, EP, tid + kChunkThreads);
+  if (tid + TH < nwv) wv1 = weight_vec<T, FULL>(a.W, a.ldw, E, EP, tid + TH);
   const T wb = tid < D ? a.W[(int64_t)tid * a.ldw + E] : T(0);
   T s0[NCH][VW], m0[NCH][VW];
   if (tid < kRowLanes) column_constants<T, NCH, VW, FULL>(a.mu, a.isg, E, l16, s0, m0);
-  for (int i = tid + 2 * kChunkThreads; i < nwv; i += kChunkThreads)   // larger models
+  for (int i = tid + 2 * TH; i < nwv; i += TH)   // larger models
     *reinterpret_cast<VecN<T, VEC>*>(Wl + i * VEC) = weight_vec<T, FULL>(a.W, a.ldw, E, EP, i);
-  for (int j = tid + kChunkThreads; j < nk; j += kChunkThreads) krv[j] = recs[ck.k0 + j];   // many small kernels
+  for (int j = tid + TH; j < nk; j += TH) krv[j] = recs[ck.k0 + j];   // many small kernels
   T ca[U][NCH][VW], cb[U][NCH][VW];
   T cya[U], cyb[U];
   load(ck, 0, ca, cya);
@@ -138,7 +163,7 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
 
   // model into LDS (once per workgroup)
   if (tid < nwv) *reinterpret_cast<VecN<T, VEC>*>(Wl + tid * VEC) = wv0;
-  if (tid + kChunkThreads < nwv) *reinterpret_cast<VecN<T, VEC>*>(Wl + (tid + kChunkThreads) * VEC) = wv1;
+  if (tid + TH < nwv) *reinterpret_cast<VecN<T, VEC>*>(Wl + (tid + TH) * VEC) = wv1;
   if (tid < D) Wb[tid] = wb;
   if (tid < kRowLanes) {
 #pragma unroll
@@ -153,7 +178,7 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
   if (tid < nk) krv[tid] = rec;
   __syncthreads();
   // each row's kernel: the last one starting at or before it
-  for (int r = tid; r < R; r += kChunkThreads) {
+  for (int r = tid; r < R; r += TH) {
     int lo = 0, hi = nk - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -171,6 +196,7 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
       const int r = base + kGroups * u + g;
       if (r >= R) break;   // uniform per 16-lane group
       const int j = rk[r];
+      if (a.kmask && !a.kmask[ck.k0 + j]) continue;   // uniform per 16-lane group
       const int B = kr[j].B;
       const int kb = kr[j].rel;
       const int S = r - kb;
@@ -188,22 +214,34 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
       const T chk = row_features<T, NCH, VW>(c[u], cy[u], s_r, m_r, z);
       bad |= !__builtin_isfinite(chk);
       const uint8_t* ops = kr[j].op;
-      int b = msb((uint32_t)S) + 1;
+      const int ms = msb((uint32_t)S);
+      int b = GRID ? 0 : ms + 1;
+      T mine = qnan<T>();   // GRID: this lane's column of the grid
       // two independent dot products at a time, each row_dot's arithmetic
       for (; b + 2 <= B; b += 2) {
         const int o0 = ops[b], o1 = ops[b + 1];
         const T p0 = row_dot<T, NCH, VW>(z, Wl + o0 * EP, l16) + Wb[o0];
         const T p1 = row_dot<T, NCH, VW>(z, Wl + o1 * EP, l16) + Wb[o1];
+        if (GRID) {
+          const T q0 = row_first(p0), q1 = row_first(p1);
+          mine = l16 == b ? q0 : l16 == b + 1 ? q1 : mine;
+        }
         if (l16 == 0) {
-          eb[kb + (S | (1 << b))] = p0;
-          eb[kb + (S | (2 << b))] = p1;
+          if (!GRID || b > ms) eb[kb + (S | (1 << b))] = p0;
+          if (!GRID || b + 1 > ms) eb[kb + (S | (2 << b))] = p1;
         }
       }
       if (b < B) {
         const int o0 = ops[b];
         const T p0 = row_dot<T, NCH, VW>(z, Wl + o0 * EP, l16) + Wb[o0];
-        if (l16 == 0) eb[kb + (S | (1 << b))] = p0;
+        if (GRID) {
+          const T q0 = row_first(p0);
+          mine = l16 == b ? q0 : mine;
+        }
+        if (l16 == 0 && (!GRID || b > ms)) eb[kb + (S | (1 << b))] = p0;
       }
+      if (GRID && l16 < a.grid_ld)
+        a.grid[(ck.row0 + r) * a.grid_ld + l16] = ((S >> l16) & 1) ? qnan<T>() : mine;
     }
   };
   // pairs of steps, no exit inside (a step past the chunk computes nothing)
@@ -219,7 +257,7 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
 
   // ---- compose: L(S) = sum over the bits b of S, ascending, of the edge
   // into S & (2^(b+1) - 1) (the fused kernel's order) ----------------------
-  for (int r = tid; r < R; r += kChunkThreads) {
+  for (int r = tid; r < R; r += TH) {
     const int j = rk[r];
     const int kb = kr[j].rel;
     const uint32_t S = (uint32_t)(r - kb);
@@ -228,13 +266,44 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
     for (int b = 0; b < B; ++b)
       if ((S >> b) & 1u) L += eb[kb + (int)(S & ((2u << b) - 1u))];
     Lb[r] = L;
-    if (a.table) a.table[ck.row0 + r] = L;
+    if (a.table && (!a.kmask || a.kmask[ck.k0 + j])) a.table[ck.row0 + r] = L;
   }
 
-  // ---- Tier 3: per kernel, one wave: per-lane best-first lists, merged --
-  if (a.idx_out) {
+  // ---- Tier 3: per kernel, one wave: per-lane best-first lists, merged;
+  // a chunk of one kernel of 256 versions or more: every wave a share of them,
+  // the waves' lists merged by the first (the top n is unique either way) ----
+  if (!GRID && a.idx_out) {
     __syncthreads();
+    if (nk == 1 && R >= 256) {
+      Entry<T> lst[KT];
+#pragma unroll
+      for (int i = 0; i < KT; ++i) lst[i] = empty_entry<T>();
+      for (int S = tid; S < R; S += TH) {
+        const T v = Lb[S];
+        if (S != 0 && v > a.tau) {
+          Entry<T> e;
+          e.v = v;
+          e.s = S;
+          list_insert<T, KT>(lst, e);
+        }
+      }
+      group_merge<T, KT>(lst, kWave);
+      Entry<T>* xw = reinterpret_cast<Entry<T>*>(eb);   // the edges are no longer read
+      static_assert(sizeof(Entry<T>) * KT * kWaves <= sizeof(T) * 256, "lists in the edges' space");
+      if (lane == 0)
+#pragma unroll
+        for (int i = 0; i < KT; ++i) xw[wave * KT + i] = lst[i];
+      __syncthreads();
+      if (wave == 0) {
+#pragma unroll
+        for (int i = 0; i < KT; ++i) lst[i] = xw[(lane % kWaves) * KT + i];
+        group_merge<T, KT>(lst, kWaves);
+        if (lane == 0) write_list<T, KT>(lst, ck.k0, a.n, a.idx_out, a.score_out, a.count_out);
+      }
+      return;
+    }
     for (int j = wave; j < nk; j += kWaves) {   // uniform per wave
+      if (a.kmask && !a.kmask[ck.k0 + j]) continue;
       const int kb = kr[j].rel;
       const int V = 1 << kr[j].B;
       Entry<T> lst[KT];
@@ -255,32 +324,37 @@ __global__ void __launch_bounds__(kChunkThreads) path_chunk_kernel(const ChunkAr
   }
 }
 
-template <typename T, int VPL, int VW, int U, int KT, bool FULL>
+template <typename T, int VPL, int VW, int U, int KT, bool FULL, int TH, bool GRID>
 hipError_t launch_chunk_k(const ChunkArgs<T>& a, size_t smem, hipStream_t s) {
-  auto kern = path_chunk_kernel<T, VPL, VW, U, KT, FULL>;
+  auto kern = path_chunk_kernel<T, VPL, VW, U, KT, FULL, TH, GRID>;
   if (smem > 64 * 1024) {
     const hipError_t e =
         hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(kern, dim3((unsigned)a.n_chunks), dim3(kChunkThreads), smem, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.n_chunks), dim3(TH), smem, s, a);
   return hipGetLastError();
 }
 
-template <typename T, int VPL, int U, int KT>
+template <typename T, int VPL, int U, int KT, int TH = kChunkThreads, bool GRID = false>
 hipError_t launch_chunk_u(const ChunkArgs<T>& a, hipStream_t s) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int EP = kRowLanes * VPL;
   const size_t smem = chunk_smem<T>(a.D, a.E, a.max_rows, a.max_nk).total;
   const bool vec_ok = (a.E % VEC) == 0 && (reinterpret_cast<uintptr_t>(a.counters) % 16) == 0;
-  if (vec_ok && a.E == EP) return launch_chunk_k<T, VPL, VEC, U, KT, true>(a, smem, s);
-  if (vec_ok) return launch_chunk_k<T, VPL, VEC, U, KT, false>(a, smem, s);
-  return launch_chunk_k<T, VPL, 1, U, KT, false>(a, smem, s);
+  if (vec_ok && a.E == EP) return launch_chunk_k<T, VPL, VEC, U, KT, true, TH, GRID>(a, smem, s);
+  if (vec_ok) return launch_chunk_k<T, VPL, VEC, U, KT, false, TH, GRID>(a, smem, s);
+  return launch_chunk_k<T, VPL, 1, U, KT, false, TH, GRID>(a, smem, s);
 }
 
 template <typename T, int VPL>
 hipError_t launch_chunk_vpl(const ChunkArgs<T>& a, int unroll, hipStream_t s) {
+  constexpr int WIDE = chunk_wide<T, VPL>();
+  if (a.grid)
+    return a.wide ? launch_chunk_u<T, VPL, 1, 4, WIDE, true>(a, s)
+                  : launch_chunk_u<T, VPL, 1, 4, kChunkThreads, true>(a, s);
+  if (a.wide) return a.n <= 4 ? launch_chunk_u<T, VPL, 1, 4, WIDE>(a, s) : launch_chunk_u<T, VPL, 1, 8, WIDE>(a, s);
   if (a.n <= 4) {
     if (unroll >= 4) return launch_chunk_u<T, VPL, 4, 4>(a, s);
     if (unroll == 2) return launch_chunk_u<T, VPL, 2, 4>(a, s);

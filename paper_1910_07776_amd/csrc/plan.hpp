@@ -69,13 +69,15 @@ struct sugg_plan {
   sugg::Chunk* d_chunks = nullptr;
   sugg::CRec* d_crec = nullptr;   // [K] each kernel's record within its chunk
   int n_chunks = 0, chunk_max_rows = 1, chunk_max_nk = 1;
+  int cus = 256;                  // compute units of the device
   bool split_ok() const { return uni_B >= 0 && uni_B <= 6 && uni_ops && d_arrivals; }
   int n_items = 0, max_item_rows = 1, max_item_kernels = 1;
   int uni_B = -1, uni_nk = 0;
   int uni_ops = 0;
   uint64_t uni_opt_lo = 0, uni_opt_hi = 0;
-  sugg::PathLaunch cfg{4, 2, 0};   // launch shape of the scoring kernel (autotuned)
+  sugg::PathLaunch cfg{4, 2, 0};   // launch shape of the scoring kernel (default_launch, set, or autotuned)
   int item_rows = 256;             // target rows of a work item (autotuned)
+  int chunk_rows = 256;            // and of a chunk (item_rows once either is set)
   // statistics workspace
   double* d_stat_partial = nullptr;
   int stat_chunks = 1;
