@@ -23,11 +23,13 @@ _DT = {torch.float32: A.SUGG_F32, torch.float64: A.SUGG_F64}
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current device's current stream as an integer (torch.cuda.current_stream()
+    # builds a Stream object: 3.0 us a call against 0.2)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    return C.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
 class Context:
