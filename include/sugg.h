@@ -471,7 +471,10 @@ SUGG_API int64_t sugg_mlp_param_count(const sugg_mlp* mlp);
 SUGG_API int32_t sugg_mlp_launch_info(const sugg_mlp* mlp, int32_t* info);
 /* Keeps a copy of params for inference (sugg_serve_query): the BF16 working
  * weights are packed from it once, and again only after another call
- * packed other parameters. */
+ * packed other parameters.  With hid = 512, in <= 512 and out a multiple of
+ * 32 it also lays them out, in device memory of their own, for the inference
+ * that takes all three layers in one launch (batches of 8192 and more, and
+ * the features-and-ranking calls at any size; same bits). */
 SUGG_API int32_t sugg_mlp_freeze(sugg_ctx* ctx, sugg_mlp* mlp, const float* params, hipStream_t stream);
 /* y = MLP(x); keep != 0 saves what sugg_mlp_backward needs. */
 SUGG_API int32_t sugg_mlp_forward(sugg_ctx* ctx, sugg_mlp* mlp, const float* params, const float* x, int32_t batch,

@@ -1019,12 +1019,9 @@ int32_t sugg_surrogate_suggest(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* m
   if (!device_ok(ctx)) return ctx->fail(SUGG_E_HIP, "cannot select device");
   // Tier 1 of each kernel's baseline version, rounded to BF16 into the
   // network's input, then the network with Tier 3 in its output layer
-  rc = ctx->hip(launch_standardize_rows_bf16((const float*)counters, (const float*)cycles, plan->d_row_off, K,
-                                             plan->E, ctx->mu32, ctx->isg32, mlp_input(mlp), in, ctx->d_status, stream),
-                "surrogate: baseline features");
-  if (rc) return rc;
-  return mlp_infer_rank_input(ctx, mlp, K, 1, ctx->params.n_suggest, (float)ctx->params.tau, (float*)table_out,
-                              idx_out, (float*)score_out, count_out, stream);
+  const MlpFeatures f{(const float*)counters, (const float*)cycles, plan->d_row_off, ctx->mu32, ctx->isg32};
+  return mlp_infer_rank_rows(ctx, mlp, f, K, 1, ctx->params.n_suggest, (float)ctx->params.tau, (float*)table_out,
+                             idx_out, (float*)score_out, count_out, stream);
 }
 
 int32_t sugg_serve_query(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* mlp, const void* counters,
@@ -1076,10 +1073,8 @@ int32_t sugg_serve_query(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* mlp, co
   // 1. standardised baseline rows, rounded to BF16 into the network's input;
   // 2. the surrogate's tables and 3. their top n (the output layer ranks in
   // its epilogue where the table is 64 or 128 wide)
-  rc = ctx->hip(launch_standardize_rows_bf16(c, cy, p->d_row_off, K, p->E, ctx->mu32, ctx->isg32, mlp_input(mlp),
-                                             in, ctx->d_status, stream),
-                "serve: baseline features");
-  if (!rc) rc = mlp_infer_rank_input(ctx, mlp, K, 1, n, (float)ctx->params.tau, w.ys, idx_out, w.sc, count_out, stream);
+  const MlpFeatures f{c, cy, p->d_row_off, ctx->mu32, ctx->isg32};
+  rc = mlp_infer_rank_rows(ctx, mlp, f, K, 1, n, (float)ctx->params.tau, w.ys, idx_out, w.sc, count_out, stream);
   // 4. the threshold band of short lists (overflow flags)
   if (!rc)
     rc = ctx->hip(launch_band<float>(w.ys, w.seg, K, 1, idx_out, count_out, n, ctx->params.tau - band, cap, w.bc,

@@ -417,4 +417,38 @@ hipError_t launch_adam_pack(const AdamPackArgs& a, int step, hipStream_t s);
 // in one launch (the gather does not depend on the update)
 hipError_t launch_adam_gather(const AdamPackArgs& a, int step, const GatherArgs& g, hipStream_t s);
 
+// ---- frozen inference in one launch (mlp_fused.hip) --------------------------
+constexpr int kFusedHidden = 512;   // the hidden width it serves
+constexpr int kFusedTile = 64;      // rows per workgroup
+typedef __bf16 frag8 __attribute__((ext_vector_type(8)));
+// The three weight matrices [N x K] (at params + off) in operand order.
+struct FragArgs {
+  const float* params;
+  int64_t off[3];
+  int N[3], K[3], steps[3];   // steps = ceil(K / 16)
+  frag8* out[3];              // [N / 32][steps][64]
+};
+hipError_t launch_mlp_frag(const FragArgs& a, hipStream_t s);
+struct FusedArgs {
+  const __bf16* xb;          // [M x in] input, or (counters non-null) Tier 1 of rows[M] of the counters
+  const float* counters;     // [N x in], 16-byte aligned
+  const float* cycles;
+  const int64_t* rows;
+  const float* mu;
+  const float* isg;
+  int32_t* status;
+  int in, out;
+  int64_t M;
+  const frag8 *w1, *w2, *w3;
+  const float *b1, *b2, *b3;
+  float* y;                  // [M x out] or null
+  int32_t* idx_out;          // null: no ranking; as GemmArgs (out 64 or 128)
+  float* score_out;
+  int32_t* count_out;
+  int n, skip;
+  float tau;
+};
+// out a multiple of 32, in of 8 up to 512
+hipError_t launch_mlp_fused(const FusedArgs& a, hipStream_t s);
+
 }  // namespace sugg

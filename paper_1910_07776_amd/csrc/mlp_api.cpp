@@ -8,7 +8,7 @@
 #include <cstdint>
 #include <new>
 
-#include "ctx.hpp"
+#include "plan.hpp"
 
 using namespace sugg;
 
@@ -29,6 +29,9 @@ struct sugg_mlp {
   int64_t part_off[3] = {};   // partial regions of the weight gradients of layers 3, 2, 1
   float* frozen = nullptr;      // inference copy of the parameters (sugg_mlp_freeze)
   bool packed_frozen = false;   // the BF16 working weights hold the frozen parameters
+  frag8* frag = nullptr;        // the frozen weights in operand order (sugg_mlp_freeze; null: widths the
+                                //   one-launch inference does not serve)
+  frag8* frag_of[3] = {};
   int32_t info[8][4] = {};   // launched GEMM instances: forward layers 1-3, then the backward's five
   int kept_batch = -1;    // batch of the last forward that kept activations
   bool have_dy = false;   // dY of that batch is in dy/dyt (from sugg_mlp_loss)
@@ -36,7 +39,7 @@ struct sugg_mlp {
     dfree(w1); dfree(w2); dfree(w2t); dfree(w3); dfree(w3t);
     dfree(xb); dfree(xt); dfree(h1); dfree(h1t); dfree(h2); dfree(h2t);
     dfree(dy); dfree(dyt); dfree(da2); dfree(da2t); dfree(da1t);
-    dfree(a1); dfree(a2); dfree(part); dfree(loss_part); dfree(ybuf); dfree(frozen); dfree(trow);
+    dfree(a1); dfree(a2); dfree(part); dfree(loss_part); dfree(ybuf); dfree(frozen); dfree(frag); dfree(trow);
   }
 };
 
@@ -75,6 +78,60 @@ GemmArgs wgrad_args(sugg_mlp* m, int region, const __bf16* A, int lda, const __b
   g.Cf = m->part + m->part_off[region];
   *job = WgradJob{g.Cf, (int64_t)M * N, *splits, dW, A, M, K, lda, db};
   return g;
+}
+
+// Widths the one-launch inference serves.
+bool fused_widths(const sugg_mlp* m) {
+  return m->hid == kFusedHidden && m->in <= 512 && m->out % 32 == 0;
+}
+
+FragArgs frag_args(const sugg_mlp* m) {
+  FragArgs f{};
+  f.params = m->frozen;
+  const int64_t off[3] = {m->off_w1, m->off_w2, m->off_w3};
+  const int N[3] = {m->hid, m->hid, m->out}, K[3] = {m->in, m->hid, m->hid};
+  for (int q = 0; q < 3; ++q) {
+    f.off[q] = off[q];
+    f.N[q] = N[q];
+    f.K[q] = K[q];
+    f.steps[q] = (K[q] + 15) / 16;
+    f.out[q] = m->frag_of[q];
+  }
+  return f;
+}
+
+// Whether a batch takes the one-launch inference: from 8192 rows (us, layer by
+// layer against one launch, 128 -> 512 -> 512 -> out: out 64, 4096 rows 21.8 /
+// 23.3, 8192 34.5 / 23.5, 65,536 116 / 81; out 1024, 4096 30.5 / 40.8, 8192
+// 46.5 / 45.5, 32,768 110 / 86; 40 -> 64, 65,536 123 / 73), and at any size
+// where it forms the features and ranks (with ranking, out 64, 1024 rows 27.6
+// / 26.0, 4096 31.9 / 26.5; out 128, 1024 rows 37.1 / 28.7).
+bool use_fused(const sugg_mlp* m, int64_t rows, bool features_and_ranking = false) {
+  return m->frag && (rows >= 8192 || features_and_ranking);
+}
+
+FusedArgs fused_args(const sugg_mlp* m, int64_t M, float* y) {
+  FusedArgs a{};
+  a.in = m->in;
+  a.out = m->out;
+  a.M = M;
+  a.w1 = m->frag_of[0];
+  a.w2 = m->frag_of[1];
+  a.w3 = m->frag_of[2];
+  a.b1 = m->frozen + m->off_b1;
+  a.b2 = m->frozen + m->off_b2;
+  a.b3 = m->frozen + m->off_b3;
+  a.y = y;
+  return a;
+}
+
+void fused_info(sugg_mlp* m) {
+  for (int l = 0; l < 3; ++l) {
+    m->info[l][0] = kFusedTile;
+    m->info[l][1] = l < 2 ? m->hid : m->out;
+    m->info[l][2] = 1;
+    m->info[l][3] = 16;
+  }
 }
 
 int check_mlp(sugg_ctx* ctx, sugg_mlp* m, int batch) {
@@ -205,6 +262,17 @@ int mlp_infer(sugg_ctx* ctx, sugg_mlp* m, const float* x, int B, float* y, hipSt
   if (!m || m->ctx != ctx) return ctx->fail(SUGG_E_ARG, "mlp missing or from another context");
   if (!m->frozen) return ctx->fail(SUGG_E_STATE, "mlp has no frozen parameters (sugg_mlp_freeze)");
   if (B < 1 || B > m->bm) return ctx->fail(SUGG_E_SHAPE, "batch %d outside [1, %d]", B, m->bm);
+  if (use_fused(m, B) && reinterpret_cast<uintptr_t>(y) % 16 == 0) {
+    hipError_t e = launch_pack(x, B, m->in, m->xb, m->in, nullptr, m->bm, s);
+    FusedArgs a = fused_args(m, B, y);
+    a.xb = m->xb;
+    if (e == hipSuccess) e = launch_mlp_fused(a, s);
+    if (e != hipSuccess) return ctx->hip(e, "mlp inference");
+    fused_info(m);
+    m->kept_batch = -1;
+    m->have_dy = false;
+    return SUGG_OK;
+  }
   return forward(ctx, m, m->frozen, x, B, y, false, nullptr, nullptr, s, !m->packed_frozen);
 }
 
@@ -213,11 +281,48 @@ namespace {
 // Inference and each row's top n of the outputs in columns >= skip above
 // tau: the output layer's epilogue ranks where the output width is 64 or
 // 128 (a tile row), otherwise the outputs go through the row ranking kernel.
-// x == nullptr: the input is already in the BF16 input buffer (mlp_input)
-int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, int B, int skip, int n, float tau, float* y,
-               int32_t* idx, float* score, int32_t* count, hipStream_t s) {
+// The input is x, or (x == nullptr) Tier 1 of the rows listed in f.
+int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, const MlpFeatures* f, int B, int skip, int n, float tau,
+               float* y, int32_t* idx, float* score, int32_t* count, hipStream_t s) {
   const int in = m->in, hid = m->hid, out = m->out;
   hipError_t e = hipSuccess;
+  const bool rank_in = out == 64 || out == 128;
+  float* yo = y ? y : m->ybuf;
+  const bool aligned = reinterpret_cast<uintptr_t>(yo) % 16 == 0 && (!f || reinterpret_cast<uintptr_t>(f->counters) % 16 == 0);
+  if (use_fused(m, B, f && rank_in) && aligned) {
+    FusedArgs a = fused_args(m, B, rank_in ? y : yo);
+    if (f) {
+      a.counters = f->counters;
+      a.cycles = f->cycles;
+      a.rows = f->rows;
+      a.mu = f->mu;
+      a.isg = f->isg;
+      a.status = ctx->d_status;
+    } else {
+      e = launch_pack(x, B, in, m->xb, in, nullptr, m->bm, s);
+      a.xb = m->xb;
+    }
+    if (rank_in) {
+      a.idx_out = idx;
+      a.score_out = score;
+      a.count_out = count;
+      a.n = n;
+      a.skip = skip;
+      a.tau = tau;
+    }
+    if (e == hipSuccess) e = launch_mlp_fused(a, s);
+    if (e == hipSuccess && !rank_in)
+      e = launch_rank<float>(yo, nullptr, B, skip, n, tau, idx, score, count, s, (int64_t)out);
+    if (e != hipSuccess) return ctx->hip(e, "mlp inference");
+    fused_info(m);
+    m->kept_batch = -1;
+    m->have_dy = false;
+    return SUGG_OK;
+  }
+  if (f) {
+    e = launch_standardize_rows_bf16(f->counters, f->cycles, f->rows, B, in, f->mu, f->isg, m->xb, in, ctx->d_status, s);
+    if (e != hipSuccess) return ctx->hip(e, "baseline features");
+  }
   if (!m->packed_frozen) e = pack_weights(m, m->frozen, s);
   if (e == hipSuccess && x) e = launch_pack(x, B, in, m->xb, in, nullptr, m->bm, s);
   if (e != hipSuccess) return ctx->hip(e, "mlp pack");
@@ -267,12 +372,10 @@ void mlp_dims(const sugg_mlp* m, int* in, int* out, int* max_batch) {
   *max_batch = m->bm;
 }
 
-__bf16* mlp_input(sugg_mlp* m) { return m->xb; }
-
-int mlp_infer_rank_input(sugg_ctx* ctx, sugg_mlp* m, int B, int skip, int n, float tau, float* y, int32_t* idx,
-                         float* score, int32_t* count, hipStream_t s) {
+int mlp_infer_rank_rows(sugg_ctx* ctx, sugg_mlp* m, const MlpFeatures& f, int B, int skip, int n, float tau, float* y,
+                        int32_t* idx, float* score, int32_t* count, hipStream_t s) {
   if (!m->frozen) return ctx->fail(SUGG_E_STATE, "mlp has no frozen parameters (sugg_mlp_freeze)");
-  return infer_rank(ctx, m, nullptr, B, skip, n, tau, y, idx, score, count, s);
+  return infer_rank(ctx, m, nullptr, &f, B, skip, n, tau, y, idx, score, count, s);
 }
 
 extern "C" {
@@ -370,6 +473,20 @@ int32_t sugg_mlp_freeze(sugg_ctx* ctx, sugg_mlp* mlp, const float* params, hipSt
   hipError_t e = hipMemcpyAsync(mlp->frozen, params, sizeof(float) * mlp->nparam, hipMemcpyDeviceToDevice, stream);
   if (e != hipSuccess) return ctx->hip(e, "frozen parameters");
   mlp->packed_frozen = false;
+  if (fused_widths(mlp)) {
+    if (!mlp->frag) {
+      FragArgs f = frag_args(mlp);
+      size_t n[3], total = 0;
+      for (int q = 0; q < 3; ++q) total += n[q] = (size_t)f.N[q] / 32 * f.steps[q] * 64;
+      e = hipMalloc((void**)&mlp->frag, sizeof(frag8) * total);
+      if (e != hipSuccess) return ctx->hip(e, "frozen weights");
+      mlp->frag_of[0] = mlp->frag;
+      mlp->frag_of[1] = mlp->frag + n[0];
+      mlp->frag_of[2] = mlp->frag + n[0] + n[1];
+    }
+    e = launch_mlp_frag(frag_args(mlp), stream);
+    if (e != hipSuccess) return ctx->hip(e, "frozen weights");
+  }
   return SUGG_OK;
 }
 
@@ -445,7 +562,7 @@ int32_t sugg_mlp_infer_rank(sugg_ctx* ctx, sugg_mlp* mlp, const float* x, int32_
   if (n < 1 || n > SUGG_MAX_SUGGEST || skip < 0 || skip >= mlp->out || !std::isfinite(tau))
     return ctx->fail(SUGG_E_ARG, "bad n, skip or tau");
   if (!device_ok(ctx)) return ctx->fail(SUGG_E_HIP, "cannot select device");
-  return infer_rank(ctx, mlp, x, batch, skip, n, tau, y, idx, score, count, stream);
+  return infer_rank(ctx, mlp, x, nullptr, batch, skip, n, tau, y, idx, score, count, stream);
 }
 
 int32_t sugg_mlp_train_epoch(sugg_ctx* ctx, sugg_mlp* mlp, float* params, float* grads, float* m, float* v,
