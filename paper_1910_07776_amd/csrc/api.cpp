@@ -542,8 +542,7 @@ namespace {
 
 template <typename T>
 int run_judge(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, const int32_t* cand, int32_t C,
-                     T* out, const T* ref, double tol, int32_t* flag, int32_t accumulate, hipStream_t s,
-                     int32_t C2 = 0, const int32_t* cand2 = nullptr, T* out2 = nullptr, const T* ref2 = nullptr) {
+              T* out, const T* ref, double tol, int32_t* flag, int32_t accumulate, hipStream_t s) {
   JudgeArgs<T> j;
   j.counters = c;
   j.cycles = cyc;
@@ -566,10 +565,6 @@ int run_judge(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, const
   j.flag = flag;
   j.accumulate = accumulate;
   j.status = ctx->d_status;
-  j.C2 = C2;
-  j.cand2 = cand2;
-  j.out2 = out2;
-  j.ref2 = ref2;
   PathArgs<T> a{};
   a.judge = &j;
   a.E = p->E;
@@ -1047,20 +1042,12 @@ int32_t sugg_serve_query(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* mlp, co
     return ctx->fail(SUGG_E_BUDGET, "model does not fit in LDS");
   if (!device_ok(ctx)) return ctx->fail(SUGG_E_HIP, "cannot select device");
   sugg_plan* p = const_cast<sugg_plan*>(plan);
-  if (!p->serve || p->serve->cap < cap) {
-    delete p->serve;
+  if (!p->serve) {
     p->serve = new (std::nothrow) ServeWs();
     if (!p->serve) return ctx->fail(SUGG_E_BUDGET, "out of host memory");
     ServeWs& w = *p->serve;
-    w.cap = cap;
-    std::vector<int64_t> seg(K + 1);
-    for (int k = 0; k <= K; ++k) seg[k] = (int64_t)k << B;
     hipError_t e = hipMalloc((void**)&w.ys, sizeof(float) * ((size_t)K << B));
     if (e == hipSuccess) e = hipMalloc((void**)&w.sc, sizeof(float) * (size_t)K * n);
-    if (e == hipSuccess) e = hipMalloc((void**)&w.br, sizeof(float) * (size_t)K * cap);
-    if (e == hipSuccess) e = hipMalloc((void**)&w.bout, sizeof(float) * (size_t)K * cap);
-    if (e == hipSuccess) e = hipMalloc((void**)&w.bc, sizeof(int32_t) * (size_t)K * cap);
-    if (e == hipSuccess) e = upload(w.seg, seg.data(), sizeof(int64_t) * (K + 1));
     if (e != hipSuccess) {
       delete p->serve;
       p->serve = nullptr;
@@ -1070,26 +1057,45 @@ int32_t sugg_serve_query(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* mlp, co
   ServeWs& w = *p->serve;
   const float* c = (const float*)counters;
   const float* cy = (const float*)cycles;
-  // 1. standardised baseline rows, rounded to BF16 into the network's input;
-  // 2. the surrogate's tables and 3. their top n (the output layer ranks in
-  // its epilogue where the table is 64 or 128 wide)
+  // 1. standardised baseline rows, rounded to BF16 into the network's input
+  // 2. the surrogate's tables (and their top n where the output layer ranks)
   const MlpFeatures f{c, cy, p->d_row_off, ctx->mu32, ctx->isg32};
-  rc = mlp_infer_rank_rows(ctx, mlp, f, K, 1, n, (float)ctx->params.tau, w.ys, idx_out, w.sc, count_out, stream);
-  // 4. the threshold band of short lists (overflow flags)
-  if (!rc)
-    rc = ctx->hip(launch_band<float>(w.ys, w.seg, K, 1, idx_out, count_out, n, ctx->params.tau - band, cap, w.bc,
-                                     w.br, flag_out, stream), "serve: band");
-  // 5. the judge on both, in one launch (plain values of the listed subsets
-  // are the answer's scores)
-  if (!rc)
-    rc = run_judge<float>(ctx, p, c, cy, idx_out, n, (float*)score_out, w.sc, tol, flag_out, 1, stream, cap, w.bc,
-                          w.bout, w.br);
-  // 6. Tier 3's contract by the plain values: listed subsets above the
-  // threshold, no band subset above it; kept lists sorted by plain value
-  if (!rc)
-    rc = ctx->hip(launch_confirm(K, n, idx_out, (float*)score_out, count_out, w.bc, w.bout, cap,
-                                 (float)ctx->params.tau, flag_out, stream), "serve: confirm");
-  // 7. the plain path for the flagged kernels
+  const bool ranked = mlp_ranks(mlp);
+  rc = mlp_infer_rank_rows(ctx, mlp, f, K, 1, n, (float)ctx->params.tau, w.ys, ranked ? idx_out : nullptr, w.sc,
+                           count_out, stream);
+  // 3. their top n, the threshold band of short lists, the judge on both
+  // (plain values of the listed subsets are the answer's scores) and Tier 3's
+  // contract by the plain values: listed subsets above the threshold, no band
+  // subset above it; kept lists sorted by plain value
+  if (!rc) {
+    ServeTailArgs t{};
+    t.ys = w.ys;
+    t.sc = ranked ? w.sc : nullptr;
+    t.counters = c;
+    t.cycles = cy;
+    t.E = p->E;
+    t.B = B;
+    t.K = K;
+    t.n = n;
+    t.cap = cap;
+    t.W = model_W<float>(ctx);
+    t.ldw = w32_ld(p->E);
+    t.mu = ctx->mu32;
+    t.isg = ctx->isg32;
+    t.row_off = p->d_row_off;
+    t.opt_off = p->d_opt_off;
+    t.opt_ids = p->d_opt_ids;
+    t.tau = (float)ctx->params.tau;
+    t.lo = ctx->params.tau - band;
+    t.tol = tol;
+    t.idx = idx_out;
+    t.score = (float*)score_out;
+    t.count = count_out;
+    t.flag = flag_out;
+    t.status = ctx->d_status;
+    rc = ctx->hip(launch_serve_tail(t, stream), "serve: judge");
+  }
+  // 4. the plain path for the flagged kernels
   if (!rc)
     rc = run_path<float>(ctx, p, c, cy, nullptr, nullptr, idx_out, (float*)score_out, count_out, n, stream, flag_out);
   return rc;

@@ -45,12 +45,6 @@ struct JudgeArgs {
   int32_t* flag;           // [K] or null: 1 where some candidate differs from ref by > tol
   int32_t accumulate;      // nonzero: keep flags already set (no clearing)
   int32_t* status;
-  // a second candidate set judged in the same launch (C2 = 0: none), with
-  // its own cand2 [K, C2], out2 and ref2, and the same flags
-  int32_t C2;
-  const int32_t* cand2;
-  T* out2;
-  const T* ref2;
 };
 
 // Arguments of the fused scoring kernel (predict / suggest).
@@ -172,11 +166,33 @@ template <typename T>
 hipError_t launch_band(const T* scores, const int64_t* seg_off, int32_t nseg, int32_t skip_head,
                        const int32_t* top_idx, const int32_t* top_count, int32_t n, double lo, int32_t C,
                        int32_t* cand_out, T* ref_out, int32_t* flag_out, hipStream_t s);
-// serving: flag kernels whose kept answer breaks Tier 3's threshold by the
-// plain values, sort the others' lists by them
-hipError_t launch_confirm(int32_t K, int32_t n, int32_t* idx, float* plain, const int32_t* count,
-                          const int32_t* band_idx, const float* band_plain, int32_t C, float tau, int32_t* flag,
-                          hipStream_t s);
+
+// A serving query between the surrogate's tables and the plain pass, a batch
+// of kernels with B optimisations each.
+constexpr int kMaxBand = 64;
+struct ServeTailArgs {
+  const float* ys;         // [K << B] the surrogate's tables
+  const float* sc;         // [K, n] values of the lists in idx / count; null: rank here
+  const float* counters;   // [K << B, E]
+  const float* cycles;
+  int32_t E, B, K, n, cap; // cap: at most this many band subsets
+  const float* W;          // [D, ldw]: E weights then the intercept
+  int32_t ldw;
+  const float* mu;
+  const float* isg;
+  const int64_t* row_off;  // [K+1]
+  const int64_t* opt_off;  // [K+1]
+  const int32_t* opt_ids;
+  float tau;
+  double lo;               // band: values from here
+  double tol;              // largest |surrogate - plain| of a kept subset
+  int32_t* idx;            // [K, n] the answer: subsets, plain values, length
+  float* score;
+  int32_t* count;
+  int32_t* flag;           // [K] 1: answer by the plain pass
+  int32_t* status;
+};
+hipError_t launch_serve_tail(const ServeTailArgs& a, hipStream_t s);
 
 // FP64 column statistics of x = ln(c / cyc) over all N rows; lcyc (nullable,
 // [N]) receives every row's ln(cyc).

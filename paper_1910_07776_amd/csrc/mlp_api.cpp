@@ -276,9 +276,11 @@ int mlp_infer(sugg_ctx* ctx, sugg_mlp* m, const float* x, int B, float* y, hipSt
   return forward(ctx, m, m->frozen, x, B, y, false, nullptr, nullptr, s, !m->packed_frozen);
 }
 
+bool mlp_ranks(const sugg_mlp* m) { return m->out == 64 || m->out == 128; }
+
 namespace {
 
-// Inference and each row's top n of the outputs in columns >= skip above
+// Inference and each row's top n (idx null: without) of the outputs in columns >= skip above
 // tau: the output layer's epilogue ranks where the output width is 64 or
 // 128 (a tile row), otherwise the outputs go through the row ranking kernel.
 // The input is x, or (x == nullptr) Tier 1 of the rows listed in f.
@@ -286,7 +288,7 @@ int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, const MlpFeatures* f,
                float* y, int32_t* idx, float* score, int32_t* count, hipStream_t s) {
   const int in = m->in, hid = m->hid, out = m->out;
   hipError_t e = hipSuccess;
-  const bool rank_in = out == 64 || out == 128;
+  const bool rank_in = idx && mlp_ranks(m);
   float* yo = y ? y : m->ybuf;
   const bool aligned = reinterpret_cast<uintptr_t>(yo) % 16 == 0 && (!f || reinterpret_cast<uintptr_t>(f->counters) % 16 == 0);
   if (use_fused(m, B, f && rank_in) && aligned) {
@@ -311,7 +313,7 @@ int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, const MlpFeatures* f,
       a.tau = tau;
     }
     if (e == hipSuccess) e = launch_mlp_fused(a, s);
-    if (e == hipSuccess && !rank_in)
+    if (e == hipSuccess && idx && !rank_in)
       e = launch_rank<float>(yo, nullptr, B, skip, n, tau, idx, score, count, s, (int64_t)out);
     if (e != hipSuccess) return ctx->hip(e, "mlp inference");
     fused_info(m);
@@ -343,7 +345,7 @@ int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, const MlpFeatures* f,
   g.bias = params + m->off_b3;
   g.Cf = y;
   g.ldcf = out;
-  if (out == 64 || out == 128) {
+  if (rank_in) {
     g.idx_out = idx;
     g.score_out = score;
     g.count_out = count;
@@ -355,7 +357,7 @@ int infer_rank(sugg_ctx* ctx, sugg_mlp* m, const float* x, const MlpFeatures* f,
   } else {
     if (!y) g.Cf = m->ybuf;
     e = launch_gemm(g, kEpiFwdOut, 1, s, m->info[2]);
-    if (e == hipSuccess)
+    if (e == hipSuccess && idx)
       e = launch_rank<float>(g.Cf, nullptr, B, skip, n, tau, idx, score, count, s, (int64_t)out);
     if (e != hipSuccess) return ctx->hip(e, "mlp layer 3 and ranking");
   }

@@ -20,12 +20,9 @@ struct sugg_graph {
 
 // Workspace of a plan's serving queries (sugg_serve_query), built on first use.
 struct ServeWs {
-  int cap = 0;
-  float *ys = nullptr, *sc = nullptr, *br = nullptr, *bout = nullptr;
-  int32_t* bc = nullptr;
-  int64_t* seg = nullptr;
+  float *ys = nullptr, *sc = nullptr;
   ~ServeWs() {
-    dfree(ys); dfree(sc); dfree(br); dfree(bout); dfree(bc); dfree(seg);
+    dfree(ys); dfree(sc);
   }
 };
 
@@ -39,8 +36,10 @@ int load_features_core(sugg_ctx* ctx, const sugg_plan* plan, const void* counter
 // array on the current device (noalloc.hip); SUGG_OK or SUGG_E_HIP
 int noalloc_scratch_setup(int device);
 void mlp_dims(const sugg_mlp* m, int* in, int* out, int* max_batch);
+// whether the output layer itself ranks (a tile row holds an output row)
+bool mlp_ranks(const sugg_mlp* m);
 // frozen inference with ranking (as sugg_mlp_infer_rank) on Tier 1 of the rows
-// listed in f.rows
+// listed in f.rows; idx null (y given): the outputs alone
 struct MlpFeatures {
   const float* counters;
   const float* cycles;

@@ -412,53 +412,6 @@ hipError_t launch_band(const T* scores, const int64_t* seg_off, int32_t nseg, in
   return hipGetLastError();
 }
 
-// Tier 3's contract on a served kernel's kept answer (Section 2: only choices
-// above the threshold, sorted by expected benefit), judged by the plain
-// values: a listed subset whose plain value is not above tau, or a band
-// subset whose plain value is above it, flags the kernel (flags already set
-// stay set); an unflagged kernel's list is sorted by its plain values
-// (descending, equal values by the smaller subset).  One thread per kernel.
-__global__ void confirm_kernel(int K, int n, int32_t* __restrict__ idx, float* __restrict__ plain,
-                               const int32_t* __restrict__ count, const int32_t* __restrict__ band_idx,
-                               const float* __restrict__ band_plain, int C, float tau, int32_t* flag) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K || flag[k]) return;
-  const int cnt = count[k] < n ? count[k] : n;
-  bool bad = false;
-  for (int i = 0; i < cnt; ++i) bad |= !(plain[(int64_t)k * n + i] > tau);
-  for (int j = 0; j < C; ++j)
-    if (band_idx[(int64_t)k * C + j] >= 0) bad |= band_plain[(int64_t)k * C + j] > tau;
-  if (bad) {
-    flag[k] = 1;
-    return;
-  }
-  // insertion sort of at most SUGG_MAX_SUGGEST entries
-  int32_t* ip = idx + (int64_t)k * n;
-  float* vp = plain + (int64_t)k * n;
-  for (int i = 1; i < cnt; ++i) {
-    const float v = vp[i];
-    const int32_t s = ip[i];
-    int j = i;
-    while (j > 0 && (vp[j - 1] < v || (vp[j - 1] == v && ip[j - 1] > s))) {
-      vp[j] = vp[j - 1];
-      ip[j] = ip[j - 1];
-      --j;
-    }
-    vp[j] = v;
-    ip[j] = s;
-  }
-}
-
-hipError_t launch_confirm(int32_t K, int32_t n, int32_t* idx, float* plain, const int32_t* count,
-                          const int32_t* band_idx, const float* band_plain, int32_t C, float tau, int32_t* flag,
-                          hipStream_t s) {
-  if (K <= 0) return hipSuccess;
-  (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(confirm_kernel, dim3((K + 255) / 256), dim3(256), 0, s, K, n, idx, plain, count, band_idx,
-                     band_plain, C, tau, flag);
-  return hipGetLastError();
-}
-
 #define SUGG_INST(T)                                                                                     \
   template hipError_t launch_colstats<T>(const T*, const T*, int64_t, int32_t, double*, int32_t, double*, \
                                          double*, T*, T*, int32_t*, hipStream_t, double*);                \
