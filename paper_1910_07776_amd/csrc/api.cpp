@@ -84,7 +84,9 @@ void build_items(const std::vector<int32_t>& nopts, const std::vector<int64_t>& 
 // Launch shape of a new plan's scoring kernel, from the batch's rows and its
 // largest kernel; chunk: rows of a streaming chunk.
 // - From 65,536 rows, and where a kernel has 128 versions or more, the
-//   streaming form, chunks of the largest kernel's size (64 to 512 rows).  us
+//   streaming form, chunks of the largest kernel's size (64 to 512 rows; from
+//   524,288 rows, where there are enough chunks, at least 128: 8192 kernels of
+//   64 versions 56.8 against 51.0 us, 16,384 of 16..64 86 / 72).  us
 //   per pass, fused shape (4 waves, 2 rows a stage) against this one, 128
 //   FP32 events: 16,384 kernels of 4..10 optimisations 493 / 441, 4096 169 /
 //   113, 256 40 / 22; 64 versions x 8192 95 / 44, x 2048 19.0 / 17.5; 16 x
@@ -97,7 +99,7 @@ void build_items(const std::vector<int32_t>& nopts, const std::vector<int64_t>& 
 //   against 6.6, x 512 9.0 against 7.5; 2 kernels of 40 FP64 events 10.0
 //   against 8.6; 256 FP32 events the other way round, 19.0 against 9.9.
 PathLaunch default_launch(int64_t rows, int Bmax, int E, int dtype, int& chunk) {
-  chunk = std::min(std::max(1 << Bmax, 64), 512);
+  chunk = std::min(std::max(1 << Bmax, rows >= (1 << 19) ? 128 : 64), 512);
   if (rows >= 65536 || Bmax >= 7) return PathLaunch{4, -2, 0};
   const int lane_bytes = (dtype == SUGG_F32 ? 4 : 8) * (E <= 64 ? 4 : E <= 128 ? 8 : 16);
   if (lane_bytes > 32) return PathLaunch{4, 2, 0};
@@ -110,8 +112,9 @@ PathLaunch default_launch(int64_t rows, int Bmax, int E, int dtype, int& chunk) 
 // versions 38 / 21, 256 41 / 31, 512 53 / 50, 1024 equal, 4096 387 / 390;
 // 4..10 optimisations, 256 kernels 39 / 22, 1000 41 / 38, 2048 63 / 66; of 256
 // versions, 512 kernels 20 / 25.  The grid of 1000 kernels of 4..10 (100
-// events) 123 / 61.  A masked pass (most chunks end at once) with 1024
-// kernels of 1024 versions 129 / 114 (the whole serving query), 4096 303 / 312.
+// events) 123 / 61.  A masked pass is as if of its selected chunks:
+// 1024 kernels of 1024 versions, 5 / 28 / 60% selected, 38 / 45 / 67 against
+// 22 / 42 / 68, 4096 44 / 133 / 243 against 38 / 149 / 257.
 bool wide_chunks(const sugg_plan* p, bool masked) {
   return p->chunk_max_rows >= 512 && p->n_chunks <= (masked ? 8 : 3) * p->cus;
 }

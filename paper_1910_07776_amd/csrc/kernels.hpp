@@ -113,7 +113,7 @@ struct alignas(16) Chunk {
 struct alignas(16) CRec {
   int16_t rel;
   int8_t B;
-  int8_t pad;
+  int8_t skip;    // 0; in a workgroup's copy 1 where a mask does not select the kernel
   uint8_t op[12];
 };
 static_assert(sizeof(CRec) == 16 && SUGG_MAX_OPTS <= 12, "chunk kernel record");

@@ -24,6 +24,7 @@ namespace sugg {
 // more than 32 bytes of a row, for its registers), which ends a large chunk
 // sooner where there are too few chunks to fill the chip.
 constexpr int kChunkThreads = 256;
+constexpr int kPackedNk = 16;   // masked passes: most kernels of a chunk whose flags a lane reads
 template <typename T, int VPL>
 constexpr int chunk_wide() { return sizeof(T) * VPL <= 32 ? 1024 : 512; }
 
@@ -82,8 +83,14 @@ __device__ __forceinline__ VecN<T, 16 / sizeof(T)> weight_vec(const T* W, int ld
 }
 
 // GRID: every optimisation a version lacks is predicted and the grid written
-// (no ranking).  With kmask, chunks without a selected kernel end at once and
-// only selected kernels' rows are used and their outputs written.
+// (no ranking).  With kmask only selected kernels' rows are used and their
+// outputs written; workgroup (j, segment) takes the j-th chunk with a selected
+// kernel of 64 consecutive ones, so the workgroups with work come first and
+// spread evenly over the chip, and the others end at once (28% of 4096 kernels
+// of 1024 versions: 178 us with one workgroup per chunk and each row's flag
+// read from memory, 174 with the packing, 132 with the flags in LDS too).
+// Chunks of many small kernels stay one workgroup each: reading 64 chunks'
+// flags would cost more than it evens out.
 template <typename T, int VPL, int VW, int U, int KT, bool FULL, int TH, bool GRID>
 __global__ void __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(
     TH == 1024 && sizeof(T) == 4 ? 8 : 1)))   // two wide FP32 workgroups per compute unit
@@ -112,16 +119,18 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   // waits only for its own rows, not for the next step's.
   constexpr int step = kGroups * U;
   auto load = [&](const Chunk& c, int base, T (&cv)[U][NCH][VW], T (&cy)[U]) {
+    const T* c0 = a.counters + c.row0 * E;
+    const T* y0 = a.cycles + c.row0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       int r = base + kGroups * u + g;
       r = r < c.R ? r : c.R - 1;
-      const T* rp = a.counters + (c.row0 + r) * E;
+      const uint32_t ro = (uint32_t)(r * E);   // below 2^20: a 32-bit offset from the chunk's uniform base
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         const int cc = (l16 + kRowLanes * ch) * VW;
         if (FULL || cc < E) {
-          const VecN<T, VW> q = *reinterpret_cast<const VecN<T, VW>*>(rp + cc);
+          const VecN<T, VW> q = *reinterpret_cast<const VecN<T, VW>*>(c0 + (ro + (uint32_t)cc));
 #pragma unroll
           for (int v = 0; v < VW; ++v) cv[u][ch][v] = q.v[v];
         } else {
@@ -129,14 +138,28 @@ path_chunk_kernel(const ChunkArgs<T> a) {
           for (int v = 0; v < VW; ++v) cv[u][ch][v] = T(1);
         }
       }
-      cy[u] = a.cycles[c.row0 + r];
+      cy[u] = y0[(uint32_t)r];
     }
   };
   const int4* recs = reinterpret_cast<const int4*>(a.recs);
   int4* krv = reinterpret_cast<int4*>(kr);
-  const Chunk ck = a.chunks[blockIdx.x];
+  int at = blockIdx.x;
+  const bool packed = a.kmask && a.max_nk <= kPackedNk;   // uniform
+  if (packed) {
+    const int nseg = (a.n_chunks + kWave - 1) / kWave, seg = at % nseg, i = seg * kWave + lane;
+    int sel = 0;
+    if (i < a.n_chunks) {
+      const Chunk c = a.chunks[i];
+      for (int j = 0; j < c.nk; ++j) sel |= a.kmask[c.k0 + j];
+    }
+    uint64_t live = __ballot(sel != 0);
+    for (int j = at / nseg; j && live; --j) live &= live - 1;
+    if (!live) return;   // uniform over the workgroup: every wave read the same flags
+    at = seg * kWave + __builtin_ctzll(live);
+  }
+  const Chunk ck = a.chunks[at];
   const int R = ck.R, nk = ck.nk;
-  if (a.kmask) {   // uniform
+  if (a.kmask && !packed) {   // uniform
     int sel = 0;
     for (int j = tid; j < nk; j += TH) sel |= a.kmask[ck.k0 + j];
     if (!__syncthreads_or(sel)) return;
@@ -144,8 +167,14 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   // loads in issue order: this chunk's kernel records and the model (small,
   // needed first), then the first two steps of rows; whatever would wait on
   // a load (a loop over a larger model or many kernels) comes before the rows
+  // a kernel's record; its spare byte is nonzero where it is not selected
+  auto chosen = [&](int j) {
+    int4 q = recs[ck.k0 + j];
+    if (a.kmask && !a.kmask[ck.k0 + j]) q.x |= 1 << 24;
+    return q;
+  };
   int4 rec = make_int4(0, 0, 0, 0);
-  if (tid < nk) rec = recs[ck.k0 + tid];
+  if (tid < nk) rec = chosen(tid);
   const int nwv = D * (EP / VEC);
   VecN<T, VEC> wv0, wv1;
   if (tid < nwv) wv0 = weight_vec<T, FULL>(a.W, a.ldw, E, EP, tid);
@@ -155,7 +184,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   if (tid < kRowLanes) column_constants<T, NCH, VW, FULL>(a.mu, a.isg, E, l16, s0, m0);
   for (int i = tid + 2 * TH; i < nwv; i += TH)   // larger models
     *reinterpret_cast<VecN<T, VEC>*>(Wl + i * VEC) = weight_vec<T, FULL>(a.W, a.ldw, E, EP, i);
-  for (int j = tid + TH; j < nk; j += TH) krv[j] = recs[ck.k0 + j];   // many small kernels
+  for (int j = tid + TH; j < nk; j += TH) krv[j] = chosen(j);   // many small kernels
   T ca[U][NCH][VW], cb[U][NCH][VW];
   T cya[U], cyb[U];
   load(ck, 0, ca, cya);
@@ -177,7 +206,9 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   bool bad = false;
   if (tid < nk) krv[tid] = rec;
   __syncthreads();
-  // each row's kernel: the last one starting at or before it
+  // each row's kernel: the last one starting at or before it; -1 for the rows
+  // of a kernel that is not selected (from LDS: a load of the flag beside the
+  // rows would wait for all the rows in flight)
   for (int r = tid; r < R; r += TH) {
     int lo = 0, hi = nk - 1;
     while (lo < hi) {
@@ -185,7 +216,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
       if (kr[mid].rel <= r) lo = mid;
       else hi = mid - 1;
     }
-    rk[r] = (int16_t)lo;
+    rk[r] = (int16_t)(kr[lo].skip ? -1 : lo);
   }
   __syncthreads();
 
@@ -196,7 +227,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
       const int r = base + kGroups * u + g;
       if (r >= R) break;   // uniform per 16-lane group
       const int j = rk[r];
-      if (a.kmask && !a.kmask[ck.k0 + j]) continue;   // uniform per 16-lane group
+      if (j < 0) continue;   // uniform per 16-lane group
       const int B = kr[j].B;
       const int kb = kr[j].rel;
       const int S = r - kb;
@@ -259,6 +290,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   // into S & (2^(b+1) - 1) (the fused kernel's order) ----------------------
   for (int r = tid; r < R; r += TH) {
     const int j = rk[r];
+    if (j < 0) continue;
     const int kb = kr[j].rel;
     const uint32_t S = (uint32_t)(r - kb);
     const int B = kr[j].B;
@@ -266,7 +298,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
     for (int b = 0; b < B; ++b)
       if ((S >> b) & 1u) L += eb[kb + (int)(S & ((2u << b) - 1u))];
     Lb[r] = L;
-    if (a.table && (!a.kmask || a.kmask[ck.k0 + j])) a.table[ck.row0 + r] = L;
+    if (a.table) a.table[ck.row0 + r] = L;
   }
 
   // ---- Tier 3: per kernel, one wave: per-lane best-first lists, merged;
@@ -303,7 +335,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
       return;
     }
     for (int j = wave; j < nk; j += kWaves) {   // uniform per wave
-      if (a.kmask && !a.kmask[ck.k0 + j]) continue;
+      if (kr[j].skip) continue;
       const int kb = kr[j].rel;
       const int V = 1 << kr[j].B;
       Entry<T> lst[KT];
@@ -333,7 +365,8 @@ hipError_t launch_chunk_k(const ChunkArgs<T>& a, size_t smem, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(kern, dim3((unsigned)a.n_chunks), dim3(TH), smem, s, a);
+  const int grid = a.kmask && a.max_nk <= kPackedNk ? (a.n_chunks + kWave - 1) / kWave * kWave : a.n_chunks;
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(TH), smem, s, a);
   return hipGetLastError();
 }
 

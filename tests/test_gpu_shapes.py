@@ -92,3 +92,37 @@ def test_allpaths_matches_the_oracle(E, f64, D, brange, K, n):
         assert int(count[k]) == len(top) and idx[k, :len(top)].tolist() == top.tolist()
         assert score[k, :len(top)].cpu().numpy().tolist() == v[top].tolist()
     ctx.close()
+
+
+@pytest.mark.parametrize("E,f64,brange,K", [(16, False, (6, 6), 8200), (20, False, (0, 4), 20001), (128, False, (10, 10), 130),
+                                            (40, True, (5, 9), 400), (33, False, (8, 8), 65)])
+def test_masked_pass_takes_exactly_the_selected_kernels(E, f64, brange, K):
+    """Masks of no kernel, one, the last, a third, whole stretches of 64
+    chunks and all: the selected kernels' outputs are the whole pass's bit for
+    bit, the others' stay as they were (chunks of one and of many kernels)."""
+    n, D = 3, 10
+    G, ctx, _, dt, _, _ = setup(E, f64, D, (4, 4), 1, n)
+    rng = np.random.default_rng(K)
+    B = rng.integers(brange[0], brange[1] + 1, K).astype(np.int32)
+    ids = np.concatenate([np.sort(rng.choice(D, b, replace=False)) for b in B]).astype(np.int32)
+    p = G.Plan(ctx, B, ids, E, D, dt)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    c = torch.empty(p.N, E, dtype=dt, device="cuda").uniform_(1.0, 1e5, generator=g)
+    cy = torch.empty(p.N, dtype=dt, device="cuda").uniform_(1e5, 1e6, generator=g)
+    full = G.suggest(ctx, p, c, cy)
+    rowk = torch.from_numpy(np.repeat(np.arange(K), 1 << B.astype(np.int64))).cuda()
+    third = (rng.random(K) < 0.3).astype(np.int32)
+    stretch = ((np.arange(K) // 64) % 2).astype(np.int32)
+    for m in (np.zeros(K), np.eye(1, K, K // 2)[0], np.eye(1, K, K - 1)[0], third, stretch, np.ones(K)):
+        mask = torch.from_numpy(m.astype(np.int32)).cuda()
+        o = {"idx": torch.full((K, n), -7, dtype=torch.int32, device="cuda"),
+             "score": torch.full((K, n), -7.0, dtype=dt, device="cuda"),
+             "count": torch.full((K,), -7, dtype=torch.int32, device="cuda"),
+             "table": torch.full((p.N,), -7.0, dtype=dt, device="cuda")}
+        G.suggest_subset(ctx, p, c, cy, mask, o)
+        for got, want, sel in zip((o["idx"], o["score"], o["count"], o["table"]), full,
+                                  (mask.bool(),) * 3 + (mask.bool()[rowk],)):
+            s = sel.view(-1, *([1] * (got.dim() - 1)))
+            assert same(got, torch.where(s, want, torch.full_like(want, -7)))
+    G.sync(ctx)
+    ctx.close()
