@@ -42,6 +42,19 @@ __device__ __forceinline__ void m5p_load_row(const TI* rp, int E, int l16, doubl
   }
 }
 
+// row_features' check without the logarithms: those of a row are all finite
+// where its counters and cycles are positive and finite.
+template <int NCH, int VW>
+__device__ __forceinline__ bool m5p_bad(const double (&c)[NCH][VW], double cy) {
+  auto ok = [](double v) { return v > 0.0 && v < __builtin_huge_val(); };
+  bool bad = !ok(cy);
+#pragma unroll
+  for (int ch = 0; ch < NCH; ++ch)
+#pragma unroll
+    for (int v = 0; v < VW; ++v) bad |= !ok(c[ch][v]);
+  return bad;
+}
+
 // Selections among a block's slots with constant indices (no dynamic
 // indexing of register arrays).
 template <typename V>
@@ -107,25 +120,33 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
   const int64_t r0 = a.row_off[k];
   const int32_t* ids = a.opt_ids + a.opt_off[k];
   const bool grid = a.grid != nullptr;
-  // 1. rows: Tier 1 features of the 16 versions into LDS
+  // 1. rows: Tier 1 features into LDS of the versions that predict anything
+  // (in edge mode those without the top optimisation, half of a kernel's
+  // rows); of the others only what their counters' check reads
   {
     const int S = S0 + g;
-    const bool live = S < (1 << B);
-    const int Sr = live ? S : S0;   // a dead row re-reads a live one and is not used
-    T s_r[NCH][VW], m_r[NCH][VW];
-    column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
-    T c[NCH][VW];
-    m5p_load_row<TI, NCH, VW>(a.counters + (r0 + Sr) * a.E, a.E, l16, c);
-    T z[NCH][VW];
-    const T chk = row_features<T, NCH, VW>(c, (T)a.cycles[r0 + Sr], s_r, m_r, z);
+    const bool live = S < (1 << B), need = m5p_row_edges(S, B, grid) > 0;
+    bool bad = false;
+    if (need || (live && l16 == 0)) {
+      T c[NCH][VW];
+      m5p_load_row<TI, NCH, VW>(a.counters + (r0 + S) * a.E, a.E, l16, c);
+      const T cy = (T)a.cycles[r0 + S];
+      if (need) {
+        T s_r[NCH][VW], m_r[NCH][VW], z[NCH][VW];
+        column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
+        const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
+        bad = l16 == 0 && !__builtin_isfinite(chk);
 #pragma unroll
-    for (int ch = 0; ch < NCH; ++ch) {
-      VecN<T, VW> q;
+        for (int ch = 0; ch < NCH; ++ch) {
+          VecN<T, VW> q;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) q.v[v] = z[ch][v];
-      *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
+          for (int v = 0; v < VW; ++v) q.v[v] = z[ch][v];
+          *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
+        }
+      } else {
+        bad = m5p_bad<NCH, VW>(c, cy);
+      }
     }
-    const bool bad = live && l16 == 0 && !__builtin_isfinite(chk);
     if (__ballot(bad) != 0 && (tid % kWave) == 0) atomicOr(a.status, (int)kStatusBadCounter);
   }
   __syncthreads();
@@ -176,85 +197,95 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
   }
 }
 
-// Small kernels (at most 64 versions), chain edges only: one workgroup per
-// kernel.  Every row's features into LDS (four rows per 16-lane group, their
-// loads in flight together), every chain edge walked at once (thread t takes
-// version t + 1), the leaf models four per group with their weight rows in
-// flight together, then Tier 3 in LDS: the composition level by level and
-// the top-n of wave 0.  The arithmetic of an edge and of the composition is
-// that of the tiled kernel and the separate composition, so both give the
-// same bits.
-template <typename TI, int VPL, int VW, int KT>
-__global__ void __launch_bounds__(kM5pThreads) m5p_small_kernel(const M5pArgs<TI> a, TI* table, int32_t* idx_out,
-                                                                TI* score_out, int32_t* count_out, int n, double tau) {
+// Batches of kernels of at most 2^MB versions (MB 4 to 7), chain edges only: one
+// workgroup of 16 threads per version without the top optimisation, for one
+// kernel.  The features of those rows (the edges start from them) into LDS,
+// one row per 16-lane group; of the other rows only what their counters' check reads.
+// Then every chain edge walked at once (thread t takes version t + 1), the
+// leaf models two per group with their weight rows in flight together, and
+// Tier 3 by the first wave: the composition and the top n.  The arithmetic of
+// an edge and of the composition is that of the tiled kernel and the separate
+// composition, so both give the same bits.
+//
+// Bound by a chain of latencies (row addresses, rows, the walk's blocks, the
+// leaf's weights) with the FP64 logarithms between: with 256 threads and the
+// features of all 64 rows, 512 kernels of 64 versions and 128 FP32 events took
+// 20.9 us, 9.9 of it features; now 15.5 (the whole call 22.3 -> 15.8; 300 of 128
+// versions by tiles and a separate composition 42, now 26; 1000 of 16 with 200
+// events 48 -> 16).
+template <typename TI, int VPL, int VW, int MB>
+__global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const M5pArgs<TI> a, TI* table,
+                                                                          int32_t* idx_out, TI* score_out,
+                                                                          int32_t* count_out, int n, double tau) {
   using T = double;
   constexpr int NCH = VPL / VW;
   constexpr int EP = kRowLanes * VPL;
-  constexpr int kRows = 64, kPer = kRows / kM5pRows;
+  constexpr int kV = 1 << MB, kRows = kV / 2;   // versions; rows that edges start from, one per group of 16 lanes
+  constexpr int kPer = kV / kRows;              // edges of a group
+  constexpr int kNv = kV > kWave ? kV / kWave : 1;   // versions of a lane of the first wave
   __shared__ __align__(32) T zl[kRows][EP];
-  __shared__ T ev[kRows];
-  __shared__ T L[kRows];
-  __shared__ int32_t e_leaf[kRows];
+  __shared__ T ev[kV];
+  __shared__ int32_t e_leaf[kV];
   const int tid = threadIdx.x, g = tid / kRowLanes, l16 = tid % kRowLanes;
   const int k = blockIdx.x;
   const int B = a.nopts[k];
-  const int V = 1 << B;
+  const int V = 1 << B, half = V > 1 ? V / 2 : 1;
   const int64_t r0 = a.row_off[k];
   const int32_t* ids = a.opt_ids + a.opt_off[k];
+  int root = 0;   // of this thread's walk
+  if (tid + 1 < V) root = ids[31 - __clz(tid + 1)];
   {
+    const bool own = g < half, more = half + g < V;   // uniform per group; for V >= 8 per wave
+    T c[NCH][VW], c2[NCH][VW], cy = T(1), cy2 = T(1);
+    if (own) {
+      m5p_load_row<TI, NCH, VW>(a.counters + (r0 + g) * a.E, a.E, l16, c);
+      cy = (T)a.cycles[r0 + g];
+    }
+    if (more && l16 == 0) {
+      m5p_load_row<TI, NCH, VW>(a.counters + (r0 + half + g) * a.E, a.E, l16, c2);
+      cy2 = (T)a.cycles[r0 + half + g];
+    }
+    if (tid + 1 < V) root = a.root[root];
     T s_r[NCH][VW], m_r[NCH][VW];
     column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
-    T c[kPer][NCH][VW], cy[kPer];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int S = g + kM5pRows * i;
-      m5p_load_row<TI, NCH, VW>(a.counters + (r0 + (S < V ? S : 0)) * a.E, a.E, l16, c[i]);
-      cy[i] = (T)a.cycles[r0 + (S < V ? S : 0)];
-    }
     bool bad = false;
-#pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-      const int S = g + kM5pRows * i;
-      // rows past the kernel's versions are not read later; for V >= 4 the
-      // test is uniform over a wave (its four groups hold rows 16 i + 4 w ..
-      // 16 i + 4 w + 3), so those waves skip the logarithms
-      if (S >= V) continue;
+    if (own) {
       T z[NCH][VW];
-      const T chk = row_features<T, NCH, VW>(c[i], cy[i], s_r, m_r, z);
+      const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
       bad |= l16 == 0 && !__builtin_isfinite(chk);
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         VecN<T, VW> q;
 #pragma unroll
         for (int v = 0; v < VW; ++v) q.v[v] = z[ch][v];
-        *reinterpret_cast<VecN<T, VW>*>(&zl[S][(l16 + kRowLanes * ch) * VW]) = q;
+        *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
       }
     }
+    if (more && l16 == 0) bad |= m5p_bad<NCH, VW>(c2, cy2);
     if (__ballot(bad) != 0 && (tid % kWave) == 0) atomicOr(a.status, (int)kStatusBadCounter);
   }
   __syncthreads();
   if (tid + 1 < V) {
     const int Sp = tid + 1, top = 31 - __clz(Sp);
-    const T* zr = zl[Sp - (1 << top)];
-    e_leaf[tid] = m5p_walk<T>(a.blocks, a.root[ids[top]], a.max_blocks, zr);
+    e_leaf[tid] = m5p_walk<T>(a.blocks, root, a.max_blocks, zl[Sp - (1 << top)]);
   }
   __syncthreads();
   {
-    const T* wrow[kPer];
+    VecN<T, VW> w[kPer][NCH];
+    T wb[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int e = g + kM5pRows * i;
-      wrow[i] = a.lw + (int64_t)(e + 1 < V ? e_leaf[e] : 0) * a.ldl;
-    }
-    VecN<T, VW> w[kPer][NCH];
-#pragma unroll
-    for (int i = 0; i < kPer; ++i)
+      const int e = g + kRows * i;
+      const int leaf = e + 1 < V ? e_leaf[e] : 0;
+      const T* wrow = a.lw + (int64_t)leaf * a.ldl;
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch)
-        w[i][ch] = *reinterpret_cast<const VecN<T, VW>*>(wrow[i] + (l16 + kRowLanes * ch) * VW);
+        w[i][ch] = *reinterpret_cast<const VecN<T, VW>*>(wrow + (l16 + kRowLanes * ch) * VW);
+      wb[i] = a.lb[leaf];
+    }
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-      const int e = g + kM5pRows * i;
+      const int e = g + kRows * i;
       if (e + 1 >= V) break;   // uniform per 16-lane group
       const int Sp = e + 1, top = 31 - __clz(Sp);
       const T* zr = zl[Sp - (1 << top)];
@@ -265,45 +296,53 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_small_kernel(const M5pArgs<TI
 #pragma unroll
         for (int v = 0; v < VW; ++v) part = fma(zq.v[v], w[i][ch].v[v], part);
       }
-      const T p = row_sum16(part) + a.lb[e_leaf[e]];
+      const T p = row_sum16(part) + wb[i];
       if (l16 == 0) ev[Sp] = p;
     }
   }
-  if (tid == 0) L[0] = T(0);
   __syncthreads();
-  for (int b = 0; b < B; ++b) {
-    const int lo = 1 << b;
-    if (tid >= lo && tid < 2 * lo) L[tid] = L[tid - lo] + ev[tid];
-    __syncthreads();
-  }
   if (tid < kWave) {
-    Entry<T> lst[KT];
+    const T none = -__builtin_huge_val();   // not above any threshold
+    T v[kNv];
 #pragma unroll
-    for (int i = 0; i < KT; ++i) lst[i] = empty_entry<T>();
-    if (tid < V) {
-      const T v = L[tid];
-      if (table) table[r0 + tid] = (TI)v;
-      if (tid != 0 && v > tau) {
-        Entry<T> e;
-        e.v = v;
-        e.s = tid;
-        list_insert<T, KT>(lst, e);
+    for (int u = 0; u < kNv; ++u) {
+      const int S = u * kWave + tid;
+      v[u] = none;
+      if (S < V) {
+        T x = T(0);   // ascending, as L[S] = L[S without its top bit] + edge
+        for (int b = 0; b < B; ++b)
+          if ((S >> b) & 1) x += ev[S & ((2 << b) - 1)];
+        if (table) table[r0 + S] = (TI)x;
+        v[u] = S != 0 && x > tau ? x : none;
       }
     }
     if (idx_out) {
-      group_merge<T, KT>(lst, kWave);
-      if (tid == 0) {
-        int cnt = 0;
+      // the best value, then the smallest version that has it, n times
+      T bv = T(0);
+      int bs = -1, cnt = 0;
+      for (; cnt < n; ++cnt) {   // uniform
+        T best = v[0];
 #pragma unroll
-        for (int i = 0; i < KT; ++i)
-          if (i < n) {
-            const bool ok = lst[i].s >= 0;
-            idx_out[(int64_t)k * n + i] = ok ? lst[i].s : -1;
-            score_out[(int64_t)k * n + i] = ok ? (TI)lst[i].v : qnan<TI>();
-            cnt += ok ? 1 : 0;
+        for (int u = 1; u < kNv; ++u) best = fmax(best, v[u]);
+        best = group_max<T>(best, kWave, tid);
+        if (!(lane_read(best, 0) > none)) break;
+        int S = -1;
+#pragma unroll
+        for (int u = 0; u < kNv; ++u) {
+          const uint64_t m = __ballot(v[u] == best);
+          if (S < 0 && m) {   // uniform
+            S = u * kWave + __builtin_ctzll(m);
+            v[u] = u * kWave + tid == S ? none : v[u];
           }
-        count_out[k] = cnt;
+        }
+        bv = tid == cnt ? best : bv;
+        bs = tid == cnt ? S : bs;
       }
+      if (tid < n) {
+        idx_out[(int64_t)k * n + tid] = bs;
+        score_out[(int64_t)k * n + tid] = bs >= 0 ? (TI)bv : qnan<TI>();
+      }
+      if (tid == 0) count_out[k] = cnt;
     }
   }
 }
@@ -318,27 +357,32 @@ hipError_t launch_m5p_vpl(const M5pArgs<TI>& a, int n_tiles, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename TI, int VPL>
-hipError_t launch_m5p_small_vpl(const M5pArgs<TI>& a, int K, TI* table, int32_t* idx, TI* score, int32_t* count,
-                                int n, double tau, hipStream_t s) {
+template <typename TI, int VPL, int MB>
+hipError_t launch_m5p_small_mb(const M5pArgs<TI>& a, int K, TI* table, int32_t* idx, TI* score, int32_t* count,
+                               int n, double tau, hipStream_t s) {
   constexpr int VEC = 16 / sizeof(TI);
   const bool vec = (a.E % VEC) == 0 && (reinterpret_cast<uintptr_t>(a.counters) % 16) == 0;
   (void)hipGetLastError();
-  const dim3 grid(K), block(kM5pThreads);
-  if (n <= 4) {
-    if (vec) hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, VEC, 4>), grid, block, 0, s, a, table, idx, score, count, n, tau);
-    else hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, 1, 4>), grid, block, 0, s, a, table, idx, score, count, n, tau);
-  } else {
-    if (vec) hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, VEC, 8>), grid, block, 0, s, a, table, idx, score, count, n, tau);
-    else hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, 1, 8>), grid, block, 0, s, a, table, idx, score, count, n, tau);
-  }
+  const dim3 grid(K), block(kRowLanes << (MB - 1));
+  if (vec) hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, VEC, MB>), grid, block, 0, s, a, table, idx, score, count, n, tau);
+  else hipLaunchKernelGGL((m5p_small_kernel<TI, VPL, 1, MB>), grid, block, 0, s, a, table, idx, score, count, n, tau);
   return hipGetLastError();
+}
+
+template <typename TI, int VPL>
+hipError_t launch_m5p_small_vpl(const M5pArgs<TI>& a, int K, TI* table, int32_t* idx, TI* score, int32_t* count,
+                                int n, double tau, hipStream_t s) {
+  if (a.Bmax <= 4) return launch_m5p_small_mb<TI, VPL, 4>(a, K, table, idx, score, count, n, tau, s);
+  if (a.Bmax == 5) return launch_m5p_small_mb<TI, VPL, 5>(a, K, table, idx, score, count, n, tau, s);
+  if (a.Bmax == 6) return launch_m5p_small_mb<TI, VPL, 6>(a, K, table, idx, score, count, n, tau, s);
+  return launch_m5p_small_mb<TI, VPL, 7>(a, K, table, idx, score, count, n, tau, s);
 }
 
 template <typename TI>
 hipError_t launch_m5p_small(const M5pArgs<TI>& a, int K, TI* table, int32_t* idx, TI* score, int32_t* count, int n,
                             double tau, hipStream_t s) {
   if (K <= 0) return hipSuccess;
+  if (a.Bmax > kM5pSmallB) return hipErrorInvalidValue;
   if (a.E <= 16 * 4) return launch_m5p_small_vpl<TI, 4>(a, K, table, idx, score, count, n, tau, s);
   if (a.E <= 16 * 8) return launch_m5p_small_vpl<TI, 8>(a, K, table, idx, score, count, n, tau, s);
   return launch_m5p_small_vpl<TI, 16>(a, K, table, idx, score, count, n, tau, s);

@@ -106,9 +106,9 @@ constexpr int kM5pRows = 16;          // versions per workgroup (16 lanes each)
 
 template <typename TI>
 hipError_t launch_m5p(const M5pArgs<TI>& a, int n_tiles, hipStream_t s);
-// Kernels of at most 64 versions, chain edges only: the whole pass (edges,
+// Kernels of at most 128 versions, chain edges only: the whole pass (edges,
 // composition, top-n) in one launch, one workgroup per kernel.
-constexpr int kM5pSmallB = 6;
+constexpr int kM5pSmallB = 7;
 template <typename TI>
 hipError_t launch_m5p_small(const M5pArgs<TI>& a, int K, TI* table, int32_t* idx, TI* score, int32_t* count, int n,
                             double tau, hipStream_t s);
