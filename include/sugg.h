@@ -505,10 +505,10 @@ SUGG_API int32_t sugg_mlp_train_step(sugg_ctx* ctx, sugg_mlp* mlp, float* params
  * sugg_mlp_train_step does with Adam step step0 + s + 1; loss of step s into
  * losses[s] (device).  Seven launches a step: three forward GEMMs, two
  * launches that each pair a weight gradient with the backward through that
- * layer, the first layer's weight gradient, one launch that finishes all
- * three weight and bias gradients and the loss, and Adam (which also
- * rewrites the BF16 working weights) together with the gather of the next
- * mini-batch (the first gather is a launch of its own).  Bit-identical to
+ * layer, the first layer's weight gradient, and one that finishes all three
+ * weight and bias gradients and the loss, applies Adam, rewrites the BF16
+ * working weights and gathers the next mini-batch (the first gather is a
+ * launch of its own).  Bit-identical to
  * train_step on the gathered batches.  perm is a
  * device int32 array of steps*batch entries; an entry outside [0, n_rows)
  * reads row 0 and the next sugg_sync reports SUGG_E_ARG.  Asynchronous. */

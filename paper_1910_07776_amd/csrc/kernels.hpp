@@ -393,8 +393,7 @@ hipError_t launch_gemm_pair(const GemmArgs& gw, int splits, const GemmArgs& gb, 
 // The end of up to three weight gradients in one launch: split-K sums (in
 // split order) of the partials part [splits x n] into out [n], and row sums
 // of the transposed BF16 activation gradient x [rows x cols] (leading
-// dimension ld; its bias gradient) into bias_out [rows]; with loss non-null
-// also the loss as launch_loss_sum.
+// dimension ld; its bias gradient) into bias_out [rows].
 struct WgradJob {
   const float* part;
   int64_t n;
@@ -407,15 +406,16 @@ struct WgradJob {
 struct FinishArgs {
   WgradJob job[3];
   int njobs;
-  const float* loss_part;   // nullable
+  const float* loss_part;   // launch_train_update: the loss as launch_loss_sum
   int loss_n;
   float loss_scale;
   float* loss;
 };
 hipError_t launch_wgrad_finish(const FinishArgs& a, hipStream_t s);
-// Adam (as launch_adam) over the surrogate's flat parameters, writing the
-// updated weights of its three layers to their BF16 working copies
-// (row-major w[l]; transposed wt[l] where non-null, leading dimension = rows)
+// Adam (as launch_adam) over the surrogate's flat parameters p (gradients in
+// g), writing the updated weights of its three layers to their BF16 working
+// copies (row-major w[l]; transposed wt[l] where non-null, leading dimension =
+// rows).
 struct AdamPackArgs {
   float* p;
   const float* g;
@@ -428,10 +428,11 @@ struct AdamPackArgs {
   __bf16* w[3];
   __bf16* wt[3];
 };
-hipError_t launch_adam_pack(const AdamPackArgs& a, int step, hipStream_t s);
-// launch_adam_pack of one step and launch_gather_pack of the next mini-batch
-// in one launch (the gather does not depend on the update)
-hipError_t launch_adam_gather(const AdamPackArgs& a, int step, const GatherArgs& g, hipStream_t s);
+// launch_wgrad_finish (three jobs, the last layer's first, whose outputs are
+// the parts of a.g; with the loss), that Adam with step's bias corrections, and
+// launch_gather_pack of the next mini-batch (nullable) in one launch.
+hipError_t launch_train_update(const AdamPackArgs& a, const FinishArgs& f, int step, const GatherArgs* next,
+                               hipStream_t s);
 
 // ---- frozen inference in one launch (mlp_fused.hip) --------------------------
 constexpr int kFusedHidden = 512;   // the hidden width it serves

@@ -483,19 +483,21 @@ hipError_t launch_gemm_rank(const GemmArgs& g, hipStream_t s, int32_t* info) {
 
 // A weight gradient (split over K) and a hidden-layer backward in one launch
 // where both run the instances of the surrogate's training shapes (a 64 x 64
-// weight-gradient tile with K stage 128; a 128 x 64 backward tile with K
-// stage 64 or 128), else in two launches; the results are the same.
+// weight-gradient tile with K stage 128; a 128 x 64 backward tile), else in two
+// launches; the results are the same.  The backward's K stage is 64: with 128
+// its operands took 104 KB of LDS, one workgroup per compute unit, and the
+// second layer's pair two rounds (18.1 us, now 15.1).
 hipError_t launch_gemm_pair(const GemmArgs& gw, int splits, const GemmArgs& gb, hipStream_t s, int32_t* info_w,
                             int32_t* info_b) {
-  const GemmPick pw = pick_gemm(kEpiWgrad, gw, splits), pb = pick_gemm(kEpiBwdHidden, gb, 1);
+  const GemmPick pw = pick_gemm(kEpiWgrad, gw, splits);
+  GemmPick pb = pick_gemm(kEpiBwdHidden, gb, 1);
+  if (pb.ex && pb.ks == 128) pb.ks = 64;
   const bool live_w = gw.M > 0 && gw.N > 0, live_b = gb.M > 0 && gb.N > 0;
   const bool w_ok = pw == GemmPick{1, 1, 128, true};
-  const bool b64 = pb == GemmPick{2, 1, 64, true}, b128 = pb == GemmPick{2, 1, 128, true};
-  if (live_w && live_b && w_ok && (b64 || b128)) {
+  if (live_w && live_b && w_ok && pb == GemmPick{2, 1, 64, true}) {
     (void)hipGetLastError();  // report only this launch's status
     const GemmGrid dw = gemm_grid(gw, pw, splits), db = gemm_grid(gb, pb, 1);
-    const hipError_t e = b64 ? launch_pair_k<kEpiWgrad, 1, 1, 128, kEpiBwdHidden, 2, 1, 64>(gw, dw, gb, db, s)
-                             : launch_pair_k<kEpiWgrad, 1, 1, 128, kEpiBwdHidden, 2, 1, 128>(gw, dw, gb, db, s);
+    const hipError_t e = launch_pair_k<kEpiWgrad, 1, 1, 128, kEpiBwdHidden, 2, 1, 64>(gw, dw, gb, db, s);
     if (e != hipSuccess) return e;
     gemm_info(pw, splits, info_w);
     gemm_info(pb, 1, info_b);
@@ -601,19 +603,9 @@ hipError_t launch_pack(const float* src, int rows, int cols, __bf16* dst, int ld
 __device__ __forceinline__ int64_t wgrad_nsum(const WgradJob& j) { return (j.n + 255) / 256; }
 __device__ __forceinline__ int64_t wgrad_blocks(const WgradJob& j) { return wgrad_nsum(j) + (j.rows + 3) / 4; }
 
-__device__ __forceinline__ void wgrad_finish_block(const WgradJob& j, int b) {
-  const int nsum = (int)wgrad_nsum(j);
-  if (b < nsum) {
-    const int64_t i = b * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= j.n) return;
-    float v = 0.0f;
-    for (int q = 0; q < j.splits; ++q) v += j.part[(int64_t)q * j.n + i];
-    j.out[i] = v;
-    return;
-  }
+// One wave: a row's sum, a bias gradient.
+__device__ __forceinline__ float bias_row_sum(const WgradJob& j, int row) {
   const int lane = threadIdx.x & 63;
-  const int row = (b - nsum) * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= j.rows) return;
   // lane sums of 8 consecutive elements per 512 (eight loads in flight),
   // then the lane tree: one fixed order
   const __bf16* xr = j.x + (int64_t)row * j.ld;
@@ -639,7 +631,23 @@ __device__ __forceinline__ void wgrad_finish_block(const WgradJob& j, int b) {
   for (int c = c0 + lane; c < j.cols; c += 64) sm += (float)xr[c];
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) sm += __shfl_xor(sm, off, 64);
-  if (lane == 0) j.bias_out[row] = sm;
+  return sm;
+}
+
+__device__ __forceinline__ void wgrad_finish_block(const WgradJob& j, int b) {
+  const int nsum = (int)wgrad_nsum(j);
+  if (b < nsum) {
+    const int64_t i = b * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= j.n) return;
+    float v = 0.0f;
+    for (int q = 0; q < j.splits; ++q) v += j.part[(int64_t)q * j.n + i];
+    j.out[i] = v;
+    return;
+  }
+  const int row = (b - nsum) * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (row >= j.rows) return;
+  const float sm = bias_row_sum(j, row);
+  if ((threadIdx.x & 63) == 0) j.bias_out[row] = sm;
 }
 
 // Loss from per-tile partial sums, in order (one block of 256 threads).
@@ -657,7 +665,7 @@ __device__ __forceinline__ void loss_block(const float* __restrict__ part, int n
   if (threadIdx.x == 0) *loss = red[0] * scale;
 }
 
-// Blocks go to the jobs in order, then one block to the loss.
+// Blocks go to the jobs in order.
 __global__ void __launch_bounds__(256) wgrad_finish_kernel(const FinishArgs a) {
   int b = blockIdx.x;
   for (int q = 0; q < a.njobs; ++q) {
@@ -668,11 +676,10 @@ __global__ void __launch_bounds__(256) wgrad_finish_kernel(const FinishArgs a) {
     }
     b -= nb;
   }
-  if (a.loss) loss_block(a.loss_part, a.loss_n, a.loss_scale, a.loss);
 }
 
 hipError_t launch_wgrad_finish(const FinishArgs& a, hipStream_t s) {
-  int64_t blocks = a.loss ? 1 : 0;
+  int64_t blocks = 0;
   for (int q = 0; q < a.njobs; ++q) blocks += (a.job[q].n + 255) / 256 + (a.job[q].rows + 3) / 4;
   if (blocks <= 0) return hipSuccess;
   (void)hipGetLastError();  // report only this launch's status
@@ -688,10 +695,9 @@ __global__ void __launch_bounds__(256) loss_sum_kernel(const float* __restrict__
 // Adam with bias correction (Kingma and Ba, 2015) on FP32 master weights:
 // one parameter, returns its new value (the one expression both Adam
 // kernels use).
-__device__ __forceinline__ float adam_update(float* __restrict__ p, const float* __restrict__ gr,
-                                             float* __restrict__ m, float* __restrict__ v, int64_t i, float lr,
-                                             float b1, float b2, float eps, float c1, float c2) {
-  const float g = gr[i];
+__device__ __forceinline__ float adam_update(float* __restrict__ p, float g, float* __restrict__ m,
+                                             float* __restrict__ v, int64_t i, float lr, float b1, float b2,
+                                             float eps, float c1, float c2) {
   const float mi = b1 * m[i] + (1.0f - b1) * g;
   const float vi = b2 * v[i] + (1.0f - b2) * g * g;
   m[i] = mi;
@@ -705,98 +711,109 @@ __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ gr,
                             float* __restrict__ v, int64_t n, float lr, float b1, float b2, float eps, float c1,
                             float c2) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    (void)adam_update(p, gr, m, v, i, lr, b1, b2, eps, c1, c2);
+    (void)adam_update(p, gr[i], m, v, i, lr, b1, b2, eps, c1, c2);
 }
 
-// Adam over the flat parameters with the three weight matrices' BF16 working
-// copies written from the updated values: blocks [0, tiles) take 32 x 32
-// tiles of the matrices (layer after layer, row-major tile order), updating
-// them and writing the row-major copy directly and the transposed copy
-// through LDS; the remaining blocks update every other parameter (the
-// biases), 256 per block.
-__device__ __forceinline__ void adam_pack_block(const AdamPackArgs& a, int tiles0, int tiles1, int tiles2, int b) {
+// The end of a training step in one launch: the gradients (as
+// wgrad_finish_kernel), Adam with them, the three weight matrices' BF16 working
+// copies from the updated values, the loss, and the gather of the next
+// mini-batch (which depends on none of these).  Blocks [0, tiles) take 32 x 32
+// tiles of the matrices (layer after layer, row-major tile order): the split-K
+// sums, the update, the row-major copy directly and the transposed one through
+// LDS; the next take the bias gradients and biases, 4 to a block; then the
+// loss, then the gather.  Bound by latency: each thread has the partials,
+// parameters and moments of its four elements in flight together.  In two
+// launches (gradients; Adam and gather) it took 8.4 + 6.8 us at the batch 4096
+// of 128 -> 512 -> 512 -> 64, and the gap between; in one 10.9.
+__device__ __forceinline__ void update_tile(const AdamPackArgs& a, const WgradJob& j, int l, int b) {
   __shared__ float tile[32][33];
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;   // 256 threads: 32 x 8
-  const int tl[3] = {tiles0, tiles1, tiles2};
-  int l = 0;
-  while (l < 3 && b >= tl[l]) b -= tl[l++];
-  if (l < 3) {
-    const int R = a.rows[l], Cc = a.cols[l], tcols = (Cc + 31) / 32;
-    const int r0 = (b / tcols) * 32, c0 = (b % tcols) * 32;
-    for (int i = ty; i < 32; i += 8) {
-      const int r = r0 + i, c = c0 + tx;
-      float w = 0.0f;
-      if (r < R && c < Cc) {
-        w = adam_update(a.p, a.g, a.m, a.v, a.off[l] + (int64_t)r * Cc + c, a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
-        a.w[l][(int64_t)r * Cc + c] = (__bf16)w;
-      }
-      tile[i][tx] = w;
+  const int R = a.rows[l], Cc = a.cols[l], tcols = (Cc + 31) / 32;
+  const int r0 = (b / tcols) * 32, c = (b % tcols) * 32 + tx;
+  int64_t e[4];
+  float g[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {   // (elements outside the matrix read its first)
+    const int r = r0 + ty + 8 * u;
+    e[u] = r < R && c < Cc ? (int64_t)r * Cc + c : 0;
+  }
+#pragma unroll 4
+  for (int q = 0; q < j.splits; ++q)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) g[u] += j.part[(int64_t)q * j.n + e[u]];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = r0 + ty + 8 * u;
+    float w = 0.0f;
+    if (r < R && c < Cc) {
+      j.out[e[u]] = g[u];
+      w = adam_update(a.p, g[u], a.m, a.v, a.off[l] + e[u], a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
+      a.w[l][e[u]] = (__bf16)w;
     }
-    if (a.wt[l]) {
-      __syncthreads();
-      for (int i = ty; i < 32; i += 8) {
-        const int c = c0 + i, r = r0 + tx;
-        if (r < R && c < Cc) a.wt[l][(int64_t)c * R + r] = (__bf16)tile[tx][i];
-      }
+    tile[ty + 8 * u][tx] = w;
+  }
+  if (!a.wt[l]) return;
+  __syncthreads();
+  const int c0 = c - tx;
+  for (int i = ty; i < 32; i += 8) {
+    const int cc = c0 + i, r = r0 + tx;
+    if (r < R && cc < Cc) a.wt[l][(int64_t)cc * R + r] = (__bf16)tile[tx][i];
+  }
+}
+
+__global__ void __launch_bounds__(256) train_update_kernel(const AdamPackArgs a, const FinishArgs f,
+                                                           const GatherArgs g, int gx) {
+  int b = blockIdx.x;
+  for (int l = 0; l < 3; ++l) {
+    const int n = ((a.rows[l] + 31) / 32) * ((a.cols[l] + 31) / 32);
+    if (b < n) {
+      update_tile(a, f.job[2 - l], l, b);   // (the jobs are in the backward's order)
+      return;
     }
+    b -= n;
+  }
+  for (int q = 0; q < 3; ++q) {
+    const WgradJob& j = f.job[q];
+    const int n = (j.rows + 3) / 4;
+    if (b < n) {
+      const int row = b * 4 + (threadIdx.x >> 6);
+      if (row >= j.rows) return;
+      const float sm = bias_row_sum(j, row);
+      if ((threadIdx.x & 63) == 0) {
+        j.bias_out[row] = sm;
+        (void)adam_update(a.p, sm, a.m, a.v, (j.bias_out - a.g) + row, a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
+      }
+      return;
+    }
+    b -= n;
+  }
+  if (b == 0) {
+    loss_block(f.loss_part, f.loss_n, f.loss_scale, f.loss);
     return;
   }
-  // the rest: parameters outside the three matrices, in order
-  const int64_t j = (int64_t)b * 256 + threadIdx.x;
-  int64_t i = j;
-  for (int q = 0; q < 3; ++q) {   // skip the matrices that come before
-    const int64_t sz = (int64_t)a.rows[q] * a.cols[q];
-    if (i >= a.off[q]) i += sz;
-  }
-  if (i < a.n) (void)adam_update(a.p, a.g, a.m, a.v, i, a.lr, a.b1, a.b2, a.eps, a.c1, a.c2);
+  --b;
+  gather_pack_tile(g, b % gx, b / gx);
 }
 
-__global__ void __launch_bounds__(256) adam_pack_kernel(const AdamPackArgs a, int tiles0, int tiles1, int tiles2) {
-  adam_pack_block(a, tiles0, tiles1, tiles2, blockIdx.x);
-}
-
-// Adam of one step and the gather of the next mini-batch (which does not
-// depend on it) in one launch: blocks [0, n_adam) update, the rest gather.
-__global__ void __launch_bounds__(256) adam_gather_kernel(const AdamPackArgs a, int tiles0, int tiles1, int tiles2,
-                                                          int n_adam, const GatherArgs g, int gx) {
-  const int b = blockIdx.x;
-  if (b < n_adam) adam_pack_block(a, tiles0, tiles1, tiles2, b);
-  else gather_pack_tile(g, (b - n_adam) % gx, (b - n_adam) / gx);
-}
-
-namespace {
-// bias corrections of the step and the block counts of the three matrices'
-// tiles and of the remaining parameters
-int adam_pack_setup(AdamPackArgs& a, int step, int (&t)[3]) {
+hipError_t launch_train_update(const AdamPackArgs& a0, const FinishArgs& f, int step, const GatherArgs* next,
+                               hipStream_t s) {
+  if (f.njobs != 3 || !f.loss) return hipErrorInvalidValue;
+  AdamPackArgs a = a0;
   a.c1 = 1.0f - powf(a.b1, (float)step);
   a.c2 = 1.0f - powf(a.b2, (float)step);
-  int64_t inside = 0;
+  int blocks = 1, gx = 1;
   for (int l = 0; l < 3; ++l) {
-    t[l] = ((a.rows[l] + 31) / 32) * ((a.cols[l] + 31) / 32);
-    inside += (int64_t)a.rows[l] * a.cols[l];
+    if (f.job[2 - l].n != (int64_t)a.rows[l] * a.cols[l]) return hipErrorInvalidValue;
+    blocks += ((a.rows[l] + 31) / 32) * ((a.cols[l] + 31) / 32) + (f.job[l].rows + 3) / 4;
   }
-  const int64_t rest = a.n - inside;
-  return t[0] + t[1] + t[2] + (int)((rest + 255) / 256);
-}
-}  // namespace
-
-hipError_t launch_adam_pack(const AdamPackArgs& a0, int step, hipStream_t s) {
-  AdamPackArgs a = a0;
-  int t[3];
-  const int blocks = adam_pack_setup(a, step, t);
+  GatherArgs g{};
+  if (next && next->rows > 0 && next->cols > 0) {
+    g = *next;
+    gx = (g.cols + 31) / 32;
+    blocks += gx * ((g.rows + 31) / 32);
+  }
   (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(adam_pack_kernel, dim3(blocks), dim3(256), 0, s, a, t[0], t[1], t[2]);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam_gather(const AdamPackArgs& a0, int step, const GatherArgs& g, hipStream_t s) {
-  if (g.rows <= 0 || g.cols <= 0) return launch_adam_pack(a0, step, s);
-  AdamPackArgs a = a0;
-  int t[3];
-  const int n_adam = adam_pack_setup(a, step, t);
-  const int gx = (g.cols + 31) / 32, gy = (g.rows + 31) / 32;
-  (void)hipGetLastError();  // report only this launch's status
-  hipLaunchKernelGGL(adam_gather_kernel, dim3(n_adam + gx * gy), dim3(256), 0, s, a, t[0], t[1], t[2], n_adam, g, gx);
+  hipLaunchKernelGGL(train_update_kernel, dim3(blocks), dim3(256), 0, s, a, f, g, gx);
   return hipGetLastError();
 }
 

@@ -212,10 +212,10 @@ int forward(sugg_ctx* ctx, sugg_mlp* m, const float* params, const float* x, int
 
 // Three launches and the finish: each layer's weight gradient shares a launch
 // with the backward through that layer (they do not depend on each other),
-// and one launch finishes all three weight and bias gradients (and, with
-// loss non-null, sums the loss partials of the forward that kept dY).
+// and one launch finishes all three weight and bias gradients.  finish
+// (nullable) receives that launch's arguments instead.
 int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grads, hipStream_t s,
-             float* loss = nullptr) {
+             FinishArgs* finish = nullptr) {
   (void)params;
   const int in = m->in, hid = m->hid, out = m->out, bm = m->bm;
   FinishArgs fa{};
@@ -243,11 +243,9 @@ int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grad
   gw = wgrad_args(m, 2, m->da1t, bm, m->xt, bm, hid, in, B, grads + m->off_w1, grads + m->off_b1, &sp, &fa.job[2]);
   e = launch_gemm(gw, kEpiWgrad, sp, s, m->info[7]);
   if (e != hipSuccess) return ctx->hip(e, "mlp backward layer 1");
-  if (loss) {
-    fa.loss_part = m->loss_part;
-    fa.loss_n = ((B + 63) / 64) * ((out + 63) / 64);
-    fa.loss_scale = 1.0f / ((float)B * (float)out);
-    fa.loss = loss;
+  if (finish) {
+    *finish = fa;
+    return SUGG_OK;
   }
   e = launch_wgrad_finish(fa, s);
   if (e != hipSuccess) return ctx->hip(e, "mlp gradients");
@@ -602,7 +600,7 @@ int32_t sugg_mlp_train_epoch(sugg_ctx* ctx, sugg_mlp* mlp, float* params, float*
     ap.wt[l] = wt[l];
   }
   // mini-batch s: rows perm[s*batch ..) gathered into the packed input (the
-  // gather of step s + 1 shares Adam's launch of step s)
+  // gather of step s + 1 shares the last launch of step s)
   auto gather = [&](int s) {
     return GatherArgs{X, n_rows, mlp->in, perm + (int64_t)s * batch, batch, mlp->xb, mlp->in, mlp->xt, mlp->bm,
                       mlp->trow, ctx->d_status};
@@ -612,10 +610,16 @@ int32_t sugg_mlp_train_epoch(sugg_ctx* ctx, sugg_mlp* mlp, float* params, float*
   for (int s = 0; s < steps; ++s) {
     rc = forward(ctx, mlp, params, nullptr, batch, mlp->ybuf, true, Y, nullptr, stream, false, mlp->trow, true);
     if (rc) return rc;
-    rc = backward(ctx, mlp, params, batch, grads, stream, losses + s);
+    FinishArgs fa;
+    rc = backward(ctx, mlp, params, batch, grads, stream, &fa);
     if (rc) return rc;
-    e = s + 1 < steps ? launch_adam_gather(ap, step0 + s + 1, gather(s + 1), stream)
-                      : launch_adam_pack(ap, step0 + s + 1, stream);
+    fa.loss_part = mlp->loss_part;
+    fa.loss_n = ((batch + 63) / 64) * ((mlp->out + 63) / 64);
+    fa.loss_scale = 1.0f / ((float)batch * (float)mlp->out);
+    fa.loss = losses + s;
+    GatherArgs next{};
+    if (s + 1 < steps) next = gather(s + 1);
+    e = launch_train_update(ap, fa, step0 + s + 1, s + 1 < steps ? &next : nullptr, stream);
     if (e != hipSuccess) return ctx->hip(e, "mlp adam");
   }
   mlp->packed_frozen = false;
