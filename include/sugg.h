@@ -466,7 +466,8 @@ SUGG_API int64_t sugg_mlp_param_count(const sugg_mlp* mlp);
  * the backward's dW3, dA2, dW2, dA1, dW1 products; columns are workgroup tile
  * rows, tile columns, K splits, and the K stage (32, 64 or 128) of the
  * variant without bounds checks where that ran, 0 where the variant with
- * bounds checks ran (all zeros for a product not launched yet).  Lets a
+ * bounds checks ran (all zeros for a product not launched yet;
+ * an epoch's one-launch output layer is not a product of this form).  Lets a
  * caller (a test) see which instances a given batch size exercises. */
 SUGG_API int32_t sugg_mlp_launch_info(const sugg_mlp* mlp, int32_t* info);
 /* Keeps a copy of params for inference (sugg_serve_query): the BF16 working
@@ -503,12 +504,14 @@ SUGG_API int32_t sugg_mlp_train_step(sugg_ctx* ctx, sugg_mlp* mlp, float* params
  * perm[s*batch .. (s+1)*batch) of X [n_rows x in] with targets the same rows
  * of Y [n_rows x out] (gathered by the first kernel, no copies), then what
  * sugg_mlp_train_step does with Adam step step0 + s + 1; loss of step s into
- * losses[s] (device).  Seven launches a step: three forward GEMMs, two
- * launches that each pair a weight gradient with the backward through that
- * layer, the first layer's weight gradient, and one that finishes all three
- * weight and bias gradients and the loss, applies Adam, rewrites the BF16
- * working weights and gathers the next mini-batch (the first gather is a
- * launch of its own).  Bit-identical to
+ * losses[s] (device).  Six launches a step with hid = 512 and out
+ * 64 or 128: two hidden layers, the output layer with the backward through
+ * it, the second layer's weight gradient paired with the backward through it,
+ * the other two weight gradients, and one that finishes all three weight and
+ * bias gradients and the loss, applies Adam, rewrites the BF16 working weights
+ * and gathers the next mini-batch (the first gather is a launch of its own;
+ * other widths take the output layer and its backward as two launches).
+ * Bit-identical to
  * train_step on the gathered batches.  perm is a
  * device int32 array of steps*batch entries; an entry outside [0, n_rows)
  * reads row 0 and the next sugg_sync reports SUGG_E_ARG.  Asynchronous. */

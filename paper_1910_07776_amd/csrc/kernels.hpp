@@ -408,6 +408,7 @@ struct FinishArgs {
   int njobs;
   const float* loss_part;   // launch_train_update: the loss as launch_loss_sum
   int loss_n;
+  int loss_quads;           // nonzero: four parts per tile, summed in order first
   float loss_scale;
   float* loss;
 };
@@ -433,6 +434,29 @@ struct AdamPackArgs {
 // launch_gather_pack of the next mini-batch (nullable) in one launch.
 hipError_t launch_train_update(const AdamPackArgs& a, const FinishArgs& f, int step, const GatherArgs* next,
                                hipStream_t s);
+
+// The output layer of a training step and the backward through it, hidden
+// width 512 (mlp_train.hip): dy [M x out], dyt (leading dimension ldt), da2
+// [M x 512], da2t and the loss in four parts per 64 x 64 tile.
+struct OutBackwardArgs {
+  const __bf16* h2;        // [M x 512]
+  const __bf16* w3;        // [out x 512]
+  const __bf16* w3t;       // [512 x out]
+  const float* b3;
+  const float* a2;         // [M x 512] pre-activations
+  const float* target;     // rows of out; row r's is trow[r] (nullable: r)
+  const int32_t* trow;
+  int M;
+  float scale;             // dY = scale * (Y - T)
+  __bf16 *dy, *dyt, *da2, *da2t;
+  int ldt;
+  float* loss_part;
+};
+hipError_t launch_out_backward(const OutBackwardArgs& a, int out, hipStream_t s);
+// Two weight gradients in one launch where both run the exact 64 x 64 tile
+// with K stage 128 (else two launches; the results are the same).
+hipError_t launch_wgrad_pair(const GemmArgs& g1, int splits1, const GemmArgs& g2, int splits2, hipStream_t s,
+                             int32_t* info1, int32_t* info2);
 
 // ---- frozen inference in one launch (mlp_fused.hip) --------------------------
 constexpr int kFusedHidden = 512;   // the hidden width it serves

@@ -508,6 +508,24 @@ hipError_t launch_gemm_pair(const GemmArgs& gw, int splits, const GemmArgs& gb, 
   return e;
 }
 
+hipError_t launch_wgrad_pair(const GemmArgs& g1, int splits1, const GemmArgs& g2, int splits2, hipStream_t s,
+                             int32_t* info1, int32_t* info2) {
+  const GemmPick p1 = pick_gemm(kEpiWgrad, g1, splits1), p2 = pick_gemm(kEpiWgrad, g2, splits2);
+  const GemmPick want{1, 1, 128, true};
+  if (g1.M > 0 && g1.N > 0 && g2.M > 0 && g2.N > 0 && p1 == want && p2 == want) {
+    (void)hipGetLastError();  // report only this launch's status
+    const hipError_t e = launch_pair_k<kEpiWgrad, 1, 1, 128, kEpiWgrad, 1, 1, 128>(g1, gemm_grid(g1, p1, splits1), g2,
+                                                                               gemm_grid(g2, p2, splits2), s);
+    if (e != hipSuccess) return e;
+    gemm_info(p1, splits1, info1);
+    gemm_info(p2, splits2, info2);
+    return hipGetLastError();
+  }
+  hipError_t e = launch_gemm(g1, kEpiWgrad, splits1, s, info1);
+  if (e == hipSuccess) e = launch_gemm(g2, kEpiWgrad, splits2, s, info2);
+  return e;
+}
+
 hipError_t launch_gemm(const GemmArgs& g, int epi, int splits, hipStream_t s, int32_t* info) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   (void)hipGetLastError();  // report only this launch's status
@@ -651,11 +669,13 @@ __device__ __forceinline__ void wgrad_finish_block(const WgradJob& j, int b) {
 }
 
 // Loss from per-tile partial sums, in order (one block of 256 threads).
+// quads: four parts per tile, added in order first.
 __device__ __forceinline__ void loss_block(const float* __restrict__ part, int n, float scale,
-                                           float* __restrict__ loss) {
+                                           float* __restrict__ loss, bool quads = false) {
   __shared__ float red[256];
   float s = 0.0f;
-  for (int i = threadIdx.x; i < n; i += 256) s += part[i];
+  for (int i = threadIdx.x; i < n; i += 256)
+    s += quads ? ((part[4 * i] + part[4 * i + 1]) + part[4 * i + 2]) + part[4 * i + 3] : part[i];
   red[threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w >= 1; w >>= 1) {
@@ -788,7 +808,7 @@ __global__ void __launch_bounds__(256) train_update_kernel(const AdamPackArgs a,
     b -= n;
   }
   if (b == 0) {
-    loss_block(f.loss_part, f.loss_n, f.loss_scale, f.loss);
+    loss_block(f.loss_part, f.loss_n, f.loss_scale, f.loss, f.loss_quads != 0);
     return;
   }
   --b;

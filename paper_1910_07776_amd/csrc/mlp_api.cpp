@@ -157,7 +157,7 @@ hipError_t pack_weights(sugg_mlp* m, const float* params, hipStream_t s) {
 // launch)
 int forward(sugg_ctx* ctx, sugg_mlp* m, const float* params, const float* x, int B, float* y, bool keep,
             const float* target, float* loss, hipStream_t s, bool pack_w = true, const int32_t* trow = nullptr,
-            bool defer_loss = false) {
+            bool defer_loss = false, bool hidden_only = false) {
   const int in = m->in, hid = m->hid, out = m->out, bm = m->bm;
   hipError_t e = hipSuccess;
   if (pack_w) e = pack_weights(m, params, s);
@@ -183,6 +183,11 @@ int forward(sugg_ctx* ctx, sugg_mlp* m, const float* params, const float* x, int
   g.ldct = bm;
   e = launch_gemm(g, kEpiFwdHidden, 1, s, m->info[1]);
   if (e != hipSuccess) return ctx->hip(e, "mlp layer 2");
+  if (hidden_only) {
+    m->kept_batch = keep ? B : -1;
+    m->have_dy = false;
+    return SUGG_OK;
+  }
   g = gemm(m->h2, hid, m->w3, hid, B, out, hid);
   g.bias = params + m->off_b3;
   g.Cf = y;
@@ -213,9 +218,10 @@ int forward(sugg_ctx* ctx, sugg_mlp* m, const float* params, const float* x, int
 // Three launches and the finish: each layer's weight gradient shares a launch
 // with the backward through that layer (they do not depend on each other),
 // and one launch finishes all three weight and bias gradients.  finish
-// (nullable) receives that launch's arguments instead.
+// (nullable) receives that launch's arguments instead.  out_done: dA2 is there
+// already (launch_out_backward); dW3 then shares the first layer's launch.
 int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grads, hipStream_t s,
-             FinishArgs* finish = nullptr) {
+             FinishArgs* finish = nullptr, bool out_done = false) {
   (void)params;
   const int in = m->in, hid = m->hid, out = m->out, bm = m->bm;
   FinishArgs fa{};
@@ -223,6 +229,8 @@ int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grad
   int sp = 1;
   GemmArgs gw = wgrad_args(m, 0, m->dyt, bm, m->h2t, bm, out, hid, B, grads + m->off_w3, grads + m->off_b3, &sp,
                            &fa.job[0]);
+  const GemmArgs gw3 = gw;
+  const int sp3 = sp;
   GemmArgs g = gemm(m->dy, out, m->w3t, out, B, hid, out);
   g.gact = m->a2;
   g.ldg = hid;
@@ -230,7 +238,7 @@ int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grad
   g.ldcb = hid;
   g.Ct = m->da2t;
   g.ldct = bm;
-  hipError_t e = launch_gemm_pair(gw, sp, g, s, m->info[3], m->info[4]);
+  hipError_t e = out_done ? hipSuccess : launch_gemm_pair(gw, sp, g, s, m->info[3], m->info[4]);
   if (e != hipSuccess) return ctx->hip(e, "mlp backward layer 3");
   gw = wgrad_args(m, 1, m->da2t, bm, m->h1t, bm, hid, hid, B, grads + m->off_w2, grads + m->off_b2, &sp, &fa.job[1]);
   g = gemm(m->da2, hid, m->w2t, hid, B, hid, hid);
@@ -241,7 +249,8 @@ int backward(sugg_ctx* ctx, sugg_mlp* m, const float* params, int B, float* grad
   e = launch_gemm_pair(gw, sp, g, s, m->info[5], m->info[6]);
   if (e != hipSuccess) return ctx->hip(e, "mlp backward layer 2");
   gw = wgrad_args(m, 2, m->da1t, bm, m->xt, bm, hid, in, B, grads + m->off_w1, grads + m->off_b1, &sp, &fa.job[2]);
-  e = launch_gemm(gw, kEpiWgrad, sp, s, m->info[7]);
+  e = out_done ? launch_wgrad_pair(gw3, sp3, gw, sp, s, m->info[3], m->info[7])
+               : launch_gemm(gw, kEpiWgrad, sp, s, m->info[7]);
   if (e != hipSuccess) return ctx->hip(e, "mlp backward layer 1");
   if (finish) {
     *finish = fa;
@@ -435,7 +444,7 @@ int32_t sugg_mlp_create(sugg_ctx* ctx, int32_t in, int32_t hidden, int32_t out, 
   A(m->a1, sizeof(float) * bm * hidden);
   A(m->a2, sizeof(float) * bm * hidden);
   A(m->part, sizeof(float) * part);
-  A(m->loss_part, sizeof(float) * ((bm + 63) / 64) * ((out + 63) / 64));
+  A(m->loss_part, sizeof(float) * 4 * ((bm + 63) / 64) * ((out + 63) / 64));
   A(m->ybuf, sizeof(float) * bm * out);
   A(m->trow, sizeof(int32_t) * bm);
   if (e != hipSuccess) {
@@ -605,14 +614,26 @@ int32_t sugg_mlp_train_epoch(sugg_ctx* ctx, sugg_mlp* mlp, float* params, float*
     return GatherArgs{X, n_rows, mlp->in, perm + (int64_t)s * batch, batch, mlp->xb, mlp->in, mlp->xt, mlp->bm,
                       mlp->trow, ctx->d_status};
   };
+  // the output layer and the backward through it in one launch
+  const bool one_out = mlp->hid == kFusedHidden && (mlp->out == 64 || mlp->out == 128);
   e = launch_gather_pack(gather(0), stream);
   if (e != hipSuccess) return ctx->hip(e, "mlp gather");
   for (int s = 0; s < steps; ++s) {
-    rc = forward(ctx, mlp, params, nullptr, batch, mlp->ybuf, true, Y, nullptr, stream, false, mlp->trow, true);
+    rc = forward(ctx, mlp, params, nullptr, batch, mlp->ybuf, true, Y, nullptr, stream, false, mlp->trow, true,
+                 one_out);
     if (rc) return rc;
+    if (one_out) {
+      OutBackwardArgs oa{mlp->h2, mlp->w3, mlp->w3t, params + mlp->off_b3, mlp->a2, Y, mlp->trow, batch,
+                         2.0f / ((float)batch * (float)mlp->out), mlp->dy, mlp->dyt, mlp->da2, mlp->da2t, mlp->bm,
+                         mlp->loss_part};
+      e = launch_out_backward(oa, mlp->out, stream);
+      if (e != hipSuccess) return ctx->hip(e, "mlp layer 3 and its backward");
+      mlp->have_dy = true;
+    }
     FinishArgs fa;
-    rc = backward(ctx, mlp, params, batch, grads, stream, &fa);
+    rc = backward(ctx, mlp, params, batch, grads, stream, &fa, one_out);
     if (rc) return rc;
+    fa.loss_quads = one_out;
     fa.loss_part = mlp->loss_part;
     fa.loss_n = ((batch + 63) / 64) * ((mlp->out + 63) / 64);
     fa.loss_scale = 1.0f / ((float)batch * (float)mlp->out);
