@@ -111,7 +111,8 @@ SUGG_API int32_t sugg_plan_max_opts(const sugg_plan* plan); /* max B_k, or -1 */
  * compose and rank it.  The split form serves sugg_suggest and sugg_predict
  * without a grid, other calls then take the fused form with unroll 1.  A new
  * plan's shape is chosen from its rows, its largest kernel and E (streaming
- * chunks then have the largest kernel's size, 64 to 512 rows, until
+ * chunks then have the largest kernel's size, 64 to 512 rows (at least 128
+ * from 524,288 rows), until
  * sugg_plan_set_items).  Results do not depend on the shape. */
 SUGG_API int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int32_t grid);
 SUGG_API int32_t sugg_plan_get_launch(const sugg_plan* plan, int32_t* waves, int32_t* unroll, int32_t* grid);
@@ -337,8 +338,9 @@ SUGG_API void sugg_graph_destroy(sugg_graph* graph);
  * paper's "mode" of real-valued labels read as their mean; equal distances:
  * the earlier stored sample, samples stored kernel by kernel, then by
  * version).  The IBK model lives beside the linear one in the context.
- * E <= 256.  Candidate distances are evaluated in FP32, the final ones in
- * FP64, labels averaged in FP64.
+ * E <= 256.  Candidate distances are formed from the FP32 vectors (products of
+ * their FP16 halves on the matrix cores, accumulated in FP32), the final ones
+ * in FP64, labels averaged in FP64.
  *
  * sugg_ibk_fit: column statistics of the training rows (as sugg_load_features
  *   FIT_STATS, kept with the IBK model), their standardised vectors, and the
@@ -353,9 +355,9 @@ SUGG_API void sugg_graph_destroy(sugg_graph* graph);
  *   (with or without the grid) builds and uploads its query lists and
  *   allocates its workspace (not inside a graph capture); later calls only
  *   enqueue kernels.
- *   The neighbours are exact: the FP32 search keeps k plus a margin of
- *   candidates (at least 6), which are re-ranked by FP64 distance between
- *   FP64 standardised features; where a bound on the FP32 error cannot
+ *   The neighbours are exact: the search keeps k plus a margin of
+ *   candidates (at least 4), which are re-ranked by FP64 distance between
+ *   FP64 standardised features; where a bound on the search's error cannot
  *   certify that the k nearest are among them, the query is searched again
  *   over all its samples in FP64 (sugg_ibk_exact_count reports how many were,
  *   in the plan's last IBK call; synchronous). */
