@@ -228,19 +228,6 @@ const float* model_W<float>(sugg_ctx* c) { return c->W32; }
 template <>
 const double* model_W<double>(sugg_ctx* c) { return c->W64; }
 
-__global__ void inv_kernel(const double* sig, double* isg, int E) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < E) isg[j] = 1.0 / sig[j];
-}
-
-__global__ void stats_to_f32_kernel(const double* mu, const double* sig, float* mu32, float* isg32, int E) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < E) {
-    mu32[j] = (float)mu[j];
-    isg32[j] = (float)(1.0 / sig[j]);
-  }
-}
-
 int ensure_stat_ws(sugg_ctx* ctx, sugg_plan* p) {
   if (p->d_stat_partial) return SUGG_OK;
   return ctx->hip(hipMalloc((void**)&p->d_stat_partial, sizeof(double) * 2 * p->E * p->stat_chunks),
@@ -403,13 +390,8 @@ int run_fit(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, hipStream_t s
   T* mu_t = (T*)(sizeof(T) == 4 ? (void*)ctx->mu32 : (void*)ctx->mu64);
   T* isg_t = (T*)(sizeof(T) == 4 ? (void*)ctx->isg32 : (void*)ctx->isg64);
   rc = ctx->hip(launch_colstats<T>(c, cyc, p->N, p->E, p->d_stat_partial, p->stat_chunks, ctx->mu64,
-                                   ctx->sig64, mu_t, isg_t, ctx->d_status, s, p->d_lcyc64), "column statistics");
-  if (rc) return rc;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(inv_kernel, dim3((p->E + 255) / 256), dim3(256), 0, s, ctx->sig64, ctx->isg64, p->E);
-  hipLaunchKernelGGL(stats_to_f32_kernel, dim3((p->E + 255) / 256), dim3(256), 0, s, ctx->mu64, ctx->sig64,
-                     ctx->mu32, ctx->isg32, p->E);
-  rc = ctx->hip(hipGetLastError(), "statistics");
+                                   ctx->sig64, mu_t, isg_t, ctx->d_status, s, p->d_lcyc64, ctx->isg64, ctx->mu32,
+                                   ctx->isg32), "column statistics");
   if (rc) return rc;
   GramArgs g;
   g.counters = c;
@@ -789,17 +771,13 @@ int load_features_core(sugg_ctx* ctx, const sugg_plan* plan, const void* counter
     if (p->dtype == SUGG_F32)
       rc = ctx->hip(launch_colstats<float>((const float*)counters, (const float*)cycles, p->N, p->E, partial,
                                            p->stat_chunks, ctx->mu64, ctx->sig64, ctx->mu32, ctx->isg32,
-                                           ctx->d_status, stream), "column statistics");
+                                           ctx->d_status, stream, nullptr, ctx->isg64, ctx->mu32, ctx->isg32),
+                    "column statistics");
     else
       rc = ctx->hip(launch_colstats<double>((const double*)counters, (const double*)cycles, p->N, p->E,
                                             partial, p->stat_chunks, ctx->mu64, ctx->sig64, ctx->mu64,
-                                            ctx->isg64, ctx->d_status, stream), "column statistics");
-    if (rc) return rc;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(inv_kernel, dim3((p->E + 255) / 256), dim3(256), 0, stream, ctx->sig64, ctx->isg64, p->E);
-    hipLaunchKernelGGL(stats_to_f32_kernel, dim3((p->E + 255) / 256), dim3(256), 0, stream, ctx->mu64, ctx->sig64,
-                       ctx->mu32, ctx->isg32, p->E);
-    rc = ctx->hip(hipGetLastError(), "statistics");
+                                            ctx->isg64, ctx->d_status, stream, nullptr, ctx->isg64, ctx->mu32,
+                                            ctx->isg32), "column statistics");
     if (rc) return rc;
     ctx->has_stats = true;
     // new statistics invalidate fitted weights

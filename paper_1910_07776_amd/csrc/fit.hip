@@ -283,18 +283,29 @@ __global__ void __launch_bounds__(256) gram_reduce_kernel(const double* __restri
   double acc[kReduceIds];
 #pragma unroll
   for (int o = 0; o < kReduceIds; ++o) acc[o] = 0.0;
-#pragma unroll 2
-  for (int q = g; q < n_work; q += G) {
-    const uint64_t mask = work[q].mask >> o0;
-    const uint64_t below = work[q].mask & ((1ull << o0) - 1ull);
-    const double* p = partial + q * stride;
-    const double v = p[i];
+  // eight chunks' elements in flight (two, as the compiler left it: 18.7 us for
+  // 512 kernels of 64 versions, now 17.3)
+  constexpr int U = 8;
+  for (int q0 = g; q0 < n_work; q0 += U * G) {
+    double v[U];
+    uint64_t m[U];
 #pragma unroll
-    for (int o = 0; o < kReduceIds; ++o)
-      if ((mask >> o) & 1ull) {
-        const int j = __popcll(below) + __popcll(mask & ((1ull << o) - 1ull));
-        acc[o] += label ? p[(int64_t)t * 256 + j * 16 + col] : v;
-      }
+    for (int u = 0; u < U; ++u) {
+      const int q = q0 + u * G;
+      v[u] = partial[(q < n_work ? q : q0) * stride + i];
+      m[u] = q < n_work ? work[q].mask : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t mask = m[u] >> o0, below = m[u] & ((1ull << o0) - 1ull);
+      const double* p = partial + (q0 + u * G) * stride;
+#pragma unroll
+      for (int o = 0; o < kReduceIds; ++o)
+        if ((mask >> o) & 1ull) {
+          const int j = __popcll(below) + __popcll(mask & ((1ull << o) - 1ull));
+          acc[o] += label ? p[(int64_t)t * 256 + j * 16 + col] : v[u];
+        }
+    }
   }
 #pragma unroll
   for (int o = 0; o < kReduceIds; ++o)
@@ -366,10 +377,11 @@ __device__ __forceinline__ void root_and_inverse(double d, double& g, double& ih
 // A = L L^T by block columns: one wave factorises the diagonal block in
 // registers (a row per lane, pivots and multipliers by lane reads), a thread
 // per row solves for the blocks below it, and the matrix cores update the
-// rest.  Then L^T w = t, block by block from the last.
+// rest, the next diagonal block first, so that its factorisation runs beside
+// the others' updates.  Then L^T w = t, block by block from the last.
 // A serial chain of E + 1 pivots bounds it: one column at a time, with three
 // barriers each and two more per column and triangular solve, took 288 us at
-// E = 128; now 84 us.
+// E = 128; in blocks 84, with the next diagonal block ahead 73 us.
 __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a, const int use_lds) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int o = blockIdx.x;
@@ -411,15 +423,52 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
   }
   __syncthreads();
   bool bad = false;
-  for (int p = 0; p < M; ++p) {
-    if (wave == 0) {
-      double* D = blk(p, p);
+  // block row bi, column bj of the trailing matrix, less the product of panel p
+  const auto update = [&](int p, int bi, int bj) {
+    const double* Li = blk(bi, p) + l16 * kBlkLd + l4;
+    const double* Lj = blk(bj, p) + l16 * kBlkLd + l4;
+    double* C = blk(bi, bj) + l4 * kBlkLd + l16;
+    doublex4 c;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c[i] = C[4 * i * kBlkLd];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-Li[4 * k], Lj[4 * k], c, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) C[4 * i * kBlkLd] = c[i];
+  };
+  for (int p = -1; p < M; ++p) {
+    if (p >= 0) {
+      if (16 * p > E) break;
+      for (int i = 16 * (p + 1) + tid; i < 16 * M; i += kSolveThreads) {
+        const double* D = blk(p, p);
+        double* X = blk(i >> 4, p) + (i & 15) * kBlkLd;
+        double x[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = X[k];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+          x[k] *= inv[16 * p + k];
+#pragma unroll
+          for (int j = k + 1; j < 16; ++j) x[j] = fma(-x[k], D[j * kBlkLd + k], x[j]);
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) X[k] = x[k];
+      }
+      __syncthreads();
+    }
+    if (wave == 0 && p + 1 < M) {   // the next diagonal block, while the others update the rest
+      if (p >= 0) {
+        update(p, p + 1, p + 1);
+        __threadfence_block();   // its lanes exchange elements below
+      }
+      const int p1 = p + 1;
+      double* D = blk(p1, p1);
       double row[16], iv = 1.0;
 #pragma unroll
       for (int k = 0; k < 16; ++k) row[k] = D[l16 * kBlkLd + k];
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        if (16 * p + k <= E) {   // the labels' row and the padding have no pivot
+        if (16 * p1 + k <= E) {   // the labels' row and the padding have no pivot
           double d = lane_value(row[k], k);
           if (!(d > 0.0)) {
             bad = true;
@@ -436,42 +485,14 @@ __global__ void __launch_bounds__(kSolveThreads) solve_kernel(const SolveArgs a,
       if (lane < 16) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) D[l16 * kBlkLd + k] = row[k];   // above the diagonal: not used
-        inv[16 * p + l16] = iv;
+        inv[16 * p1 + l16] = iv;
       }
     }
-    __syncthreads();
-    if (16 * p > E) break;
-    for (int i = 16 * (p + 1) + tid; i < 16 * M; i += kSolveThreads) {
-      const double* D = blk(p, p);
-      double* X = blk(i >> 4, p) + (i & 15) * kBlkLd;
-      double x[16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) x[k] = X[k];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        x[k] *= inv[16 * p + k];
-#pragma unroll
-        for (int j = k + 1; j < 16; ++j) x[j] = fma(-x[k], D[j * kBlkLd + k], x[j]);
-      }
-#pragma unroll
-      for (int k = 0; k < 16; ++k) X[k] = x[k];
-    }
-    __syncthreads();
-    int t = 0;
-    for (int bi = p + 1; bi < M; ++bi) {
-      const double* Li = blk(bi, p) + l16 * kBlkLd + l4;
-      for (int bj = p + 1; bj <= bi; ++bj, ++t) {
-        if (t % (kSolveThreads / 64) != wave) continue;
-        const double* Lj = blk(bj, p) + l16 * kBlkLd + l4;
-        double* C = blk(bi, bj) + l4 * kBlkLd + l16;
-        doublex4 c;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) c[i] = C[4 * i * kBlkLd];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) c = __builtin_amdgcn_mfma_f64_16x16x4f64(-Li[4 * k], Lj[4 * k], c, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) C[4 * i * kBlkLd] = c[i];
-      }
+    if (wave != 0 && p >= 0) {
+      int t = 0;
+      for (int bi = p + 2; bi < M; ++bi)
+        for (int bj = p + 1; bj <= bi; ++bj, ++t)
+          if (t % (kSolveThreads / 64 - 1) == wave - 1) update(p, bi, bj);
     }
     __syncthreads();
   }

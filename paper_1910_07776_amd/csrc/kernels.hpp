@@ -195,11 +195,13 @@ struct ServeTailArgs {
 hipError_t launch_serve_tail(const ServeTailArgs& a, hipStream_t s);
 
 // FP64 column statistics of x = ln(c / cyc) over all N rows; lcyc (nullable,
-// [N]) receives every row's ln(cyc).
+// [N]) receives every row's ln(cyc); isg64, mu32, isg32 (all or none) further
+// copies of the statistics.
 template <typename T>
 hipError_t launch_colstats(const T* counters, const T* cycles, int64_t N, int32_t E,
                            double* partial, int32_t nchunks, double* mu64, double* sig64,
-                           T* mu_t, T* isg_t, int32_t* status, hipStream_t s, double* lcyc = nullptr);
+                           T* mu_t, T* isg_t, int32_t* status, hipStream_t s, double* lcyc = nullptr,
+                           double* isg64 = nullptr, float* mu32 = nullptr, float* isg32 = nullptr);
 int colstats_chunks(int64_t N);
 
 // z = (x - mu) / sigma in the plan dtype.

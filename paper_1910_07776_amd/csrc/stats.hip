@@ -135,7 +135,8 @@ __global__ void __launch_bounds__(kStatThreads) colstats_partial_kernel(
 template <typename T>
 __global__ void __launch_bounds__(256) colstats_final_kernel(const T* __restrict__ c, const T* __restrict__ cyc, int64_t N,
                                       int E, const double* __restrict__ partial, int nchunks,
-                                      double* mu64, double* sig64, T* mu_t, T* isg_t) {
+                                      double* mu64, double* sig64, T* mu_t, T* isg_t, double* isg64, float* mu32,
+                                      float* isg32) {
   __shared__ double red[32][8][2];
   const int jl = threadIdx.x & 7, sl = threadIdx.x >> 3;
   const int j = blockIdx.x * 8 + jl;
@@ -167,12 +168,17 @@ __global__ void __launch_bounds__(256) colstats_final_kernel(const T* __restrict
   sig64[j] = sg;
   mu_t[j] = (T)mu;
   isg_t[j] = (T)(1.0 / sg);
+  if (isg64) {   // the context's copies of both types
+    isg64[j] = 1.0 / sg;
+    mu32[j] = (float)mu;
+    isg32[j] = (float)(1.0 / sg);
+  }
 }
 
 template <typename T>
 hipError_t launch_colstats(const T* counters, const T* cycles, int64_t N, int32_t E, double* partial,
                            int32_t nchunks, double* mu64, double* sig64, T* mu_t, T* isg_t,
-                           int32_t* status, hipStream_t s, double* lcyc) {
+                           int32_t* status, hipStream_t s, double* lcyc, double* isg64, float* mu32, float* isg32) {
   if (N <= 0) return hipErrorInvalidValue;
   const int64_t per = (N + nchunks - 1) / nchunks;
   const int used = (int)((N + per - 1) / per);
@@ -193,7 +199,7 @@ hipError_t launch_colstats(const T* counters, const T* cycles, int64_t N, int32_
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(colstats_final_kernel<T>, dim3((E + 7) / 8), dim3(256), 0, s, counters, cycles,
-                     N, (int)E, partial, used, mu64, sig64, mu_t, isg_t);
+                     N, (int)E, partial, used, mu64, sig64, mu_t, isg_t, isg64, mu32, isg32);
   return hipGetLastError();
 }
 
@@ -414,7 +420,7 @@ hipError_t launch_band(const T* scores, const int64_t* seg_off, int32_t nseg, in
 
 #define SUGG_INST(T)                                                                                     \
   template hipError_t launch_colstats<T>(const T*, const T*, int64_t, int32_t, double*, int32_t, double*, \
-                                         double*, T*, T*, int32_t*, hipStream_t, double*);                \
+                                         double*, T*, T*, int32_t*, hipStream_t, double*, double*, float*, float*); \
   template hipError_t launch_standardize<T>(const T*, const T*, int64_t, int32_t, const T*, const T*, T*, \
                                             int32_t*, hipStream_t);                                       \
   template hipError_t launch_standardize_rows<T>(const T*, const T*, const int64_t*, int64_t, int32_t, const T*, \
