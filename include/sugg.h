@@ -111,9 +111,10 @@ SUGG_API int32_t sugg_plan_max_opts(const sugg_plan* plan); /* max B_k, or -1 */
  * compose and rank it.  The split form serves sugg_suggest and sugg_predict
  * without a grid, other calls then take the fused form with unroll 1.  A new
  * plan's shape is chosen from its rows, its largest kernel and E (streaming
- * chunks then have the largest kernel's size, 64 to 512 rows (at least 128
- * from 524,288 rows), until
- * sugg_plan_set_items).  Results do not depend on the shape. */
+ * chunks then have the largest kernel's size, 64 to 512 rows, more in large
+ * batches, until sugg_plan_set_items; where that shape is the fused one for a
+ * batch of 65,536 rows or more, its grid and masked passes still stream until
+ * the shape is set or tuned).  Results do not depend on the shape. */
 SUGG_API int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int32_t grid);
 SUGG_API int32_t sugg_plan_get_launch(const sugg_plan* plan, int32_t* waves, int32_t* unroll, int32_t* grid);
 

@@ -93,17 +93,28 @@ void build_items(const std::vector<int32_t>& nopts, const std::vector<int64_t>& 
 //   65,536 162 / 132; 256 x 2048 95 / 46, x 16 16.1 / 12.9; 1024 x 4096 429 /
 //   383.  40 events, 4096 kernels of 4..10 107 / 47; 128 FP64 events, 256 of
 //   4..8 36 / 30.
+//   Lanes of more than 32 bytes of a row take 128 from 131,072 rows: 256 FP32
+//   events, 130,000 rows of 64 versions 31.8 / 26.1, 450,000 97 / 85.
+// - But FP32 batches of kernels of up to 64 versions whose items are all
+//   resident at once (resident_items) stay fused, 4 waves, 2 rows a stage:
+//   128 events, 66,000 rows of 16 versions 17.6 (streaming) / 14.0, 130,000
+//   28.2 / 18.4, 260,000 of 16..64 38.9 / 33.4; 40 events 21.3 / 14.0 at
+//   130,000; a second round of items costs 40 us (300,000 rows 53 / 71).
 // - Smaller batches of smaller kernels: the fused form with 8 waves a
 //   workgroup where a lane holds at most 32 bytes of a row (one or two rows a
 //   stage), else 4 waves: 64 versions x 1 kernel 7.8 against 6.3 us, x 64 7.4
 //   against 6.6, x 512 9.0 against 7.5; 2 kernels of 40 FP64 events 10.0
 //   against 8.6; 256 FP32 events the other way round, 19.0 against 9.9.
 PathLaunch default_launch(int64_t rows, int Bmax, int E, int dtype, int& chunk) {
-  chunk = std::min(std::max(1 << Bmax, rows >= (1 << 19) ? 128 : 64), 512);
-  if (rows >= 65536 || Bmax >= 7) return PathLaunch{4, -2, 0};
   const int lane_bytes = (dtype == SUGG_F32 ? 4 : 8) * (E <= 64 ? 4 : E <= 128 ? 8 : 16);
+  chunk = std::min(std::max(1 << Bmax, rows >= (lane_bytes > 32 ? 1 << 17 : 1 << 19) ? 128 : 64), 512);
+  if (rows >= 65536 || Bmax >= 7) return PathLaunch{4, -2, 0};
   if (lane_bytes > 32) return PathLaunch{4, 2, 0};
   return PathLaunch{8, dtype == SUGG_F32 ? 1 : 2, 0};
+}
+
+bool resident_items(const sugg_plan* p) {
+  return p->dtype == SUGG_F32 && p->E <= 128 && p->Bmax <= 6 && p->N >= 65536 && p->n_items <= 4 * p->cus;
 }
 
 // Wide workgroups for the streaming form where its chunks are large and few:
@@ -486,7 +497,7 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
   a.status = ctx->d_status;
   if (p->cfg.unroll == 0 && p->split_ok() && !grid && !kmask)
     return ctx->hip(launch_path_split<T>(a, p->d_arrivals, (T*)p->d_split_edges, s), "scoring kernel");
-  if (p->cfg.unroll < 0 &&
+  if ((p->cfg.unroll < 0 || (p->stream_others && (grid || kmask))) &&
       path_chunk_lds(sizeof(T), ctx->D, p->E, p->chunk_max_rows, p->chunk_max_nk) <= kLdsPerWorkgroup) {
     ChunkArgs<T> ch;
     ch.counters = c;
@@ -513,7 +524,7 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
     ch.n = n;
     ch.tau = (T)ctx->params.tau;
     ch.status = ctx->d_status;
-    return ctx->hip(launch_path_chunks<T>(ch, -p->cfg.unroll, s), "scoring kernel (streaming form)");
+    return ctx->hip(launch_path_chunks<T>(ch, p->cfg.unroll < 0 ? -p->cfg.unroll : 2, s), "scoring kernel (streaming form)");
   }
   PathLaunch cfg = p->cfg;
   if (cfg.unroll <= 0) cfg.unroll = 1;   // the split or streaming form does not apply: fused, one row per stage
@@ -709,6 +720,10 @@ int32_t sugg_plan_create(sugg_ctx* ctx, int32_t K, int32_t E, int32_t D, int32_t
   int chunk = target;
   p->cfg = default_launch(p->N, p->Bmax, E, dtype, chunk);
   hipError_t e = plan_items(p, target, chunk);
+  if (e == hipSuccess && p->cfg.unroll < 0 && resident_items(p)) {
+    p->cfg = PathLaunch{4, 2, 0};
+    p->stream_others = true;
+  }
   if (e == hipSuccess) e = upload(p->d_row_off, p->row_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_off, p->opt_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_ids, p->opt_ids.data(), sizeof(int32_t) * nid);
@@ -1105,6 +1120,7 @@ int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int
   if (waves < 1 || waves > 8 || grid < 0) return SUGG_E_ARG;
   if (unroll != 0 && unroll != 1 && unroll != 2 && unroll != 4 && unroll != -1 && unroll != -2 && unroll != -4)
     return SUGG_E_ARG;
+  plan->stream_others = false;
   plan->cfg.waves = waves;
   plan->cfg.unroll = unroll;
   plan->cfg.grid = grid;
@@ -1243,6 +1259,7 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
     }
   }
   plan->cfg = e == hipSuccess ? best : keep;
+  if (e == hipSuccess) plan->stream_others = false;   // the tuned shape for every pass
   const hipError_t e2 = e == hipSuccess ? set_items(best_items, best_items) : set_items(keep_items, keep_chunk);
   if (e == hipSuccess) e = e2;
   if (e0) (void)hipEventDestroy(e0);

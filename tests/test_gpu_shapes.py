@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
 CASES = [(1, False, 3, (0, 3), 9, 3), (40, True, 6, (6, 6), 2, 3), (64, False, 7, (7, 7), 3, 8), (65, True, 8, (7, 8), 5, 3),
          (128, False, 6, (6, 6), 700, 3), (128, False, 10, (10, 10), 3, 8), (100, False, 10, (9, 10), 40, 3),
          (101, False, 10, (4, 9), 300, 3), (256, False, 9, (9, 9), 7, 3), (200, True, 10, (8, 10), 12, 8),
-         (33, False, 12, (12, 12), 2, 3), (128, False, 9, (9, 9), 1000, 3), (16, True, 11, (5, 11), 60, 8)]
+         (33, False, 12, (12, 12), 2, 3), (128, False, 9, (9, 9), 1000, 3), (16, True, 11, (5, 11), 60, 8),
+         (128, False, 6, (4, 6), 1900, 3), (40, False, 6, (6, 6), 4150, 3), (150, False, 6, (5, 6), 2900, 3)]
 
 
 def setup(E, f64, D, brange, K, n):
