@@ -1043,7 +1043,8 @@ int32_t sugg_serve_query(sugg_ctx* ctx, const sugg_plan* plan, sugg_mlp* mlp, co
     if (!p->serve) return ctx->fail(SUGG_E_BUDGET, "out of host memory");
     ServeWs& w = *p->serve;
     hipError_t e = hipMalloc((void**)&w.ys, sizeof(float) * ((size_t)K << B));
-    if (e == hipSuccess) e = hipMalloc((void**)&w.sc, sizeof(float) * (size_t)K * n);
+    // for the longest lists: n_suggest may be raised between two queries
+    if (e == hipSuccess) e = hipMalloc((void**)&w.sc, sizeof(float) * (size_t)K * SUGG_MAX_SUGGEST);
     if (e != hipSuccess) {
       delete p->serve;
       p->serve = nullptr;
