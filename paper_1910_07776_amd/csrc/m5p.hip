@@ -122,12 +122,12 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
   const bool grid = a.grid != nullptr;
   // 1. rows: Tier 1 features into LDS of the versions that predict anything
   // (in edge mode those without the top optimisation, half of a kernel's
-  // rows); of the others only what their counters' check reads
+  // rows); the others' counters are only checked
   {
     const int S = S0 + g;
     const bool live = S < (1 << B), need = m5p_row_edges(S, B, grid) > 0;
     bool bad = false;
-    if (need || (live && l16 == 0)) {
+    if (live) {
       T c[NCH][VW];
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + S) * a.E, a.E, l16, c);
       const T cy = (T)a.cycles[r0 + S];
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
         T s_r[NCH][VW], m_r[NCH][VW], z[NCH][VW];
         column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
         const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
-        bad = l16 == 0 && !__builtin_isfinite(chk);
+        bad = !__builtin_isfinite(chk);
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
           VecN<T, VW> q;
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
 // Batches of kernels of at most 2^MB versions (MB 4 to 7), chain edges only: one
 // workgroup of 16 threads per version without the top optimisation, for one
 // kernel.  The features of those rows (the edges start from them) into LDS,
-// one row per 16-lane group; of the other rows only what their counters' check reads.
+// one row per 16-lane group; the other rows' counters are only checked.
 // Then every chain edge walked at once (thread t takes version t + 1), the
 // leaf models two per group with their weight rows in flight together, and
 // Tier 3 by the first wave: the composition and the top n.  The arithmetic of
@@ -241,7 +241,7 @@ __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const 
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + g) * a.E, a.E, l16, c);
       cy = (T)a.cycles[r0 + g];
     }
-    if (more && l16 == 0) {
+    if (more) {
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + half + g) * a.E, a.E, l16, c2);
       cy2 = (T)a.cycles[r0 + half + g];
     }
@@ -252,7 +252,7 @@ __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const 
     if (own) {
       T z[NCH][VW];
       const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
-      bad |= l16 == 0 && !__builtin_isfinite(chk);
+      bad |= !__builtin_isfinite(chk);
 #pragma unroll
       for (int ch = 0; ch < NCH; ++ch) {
         VecN<T, VW> q;
@@ -261,7 +261,7 @@ __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const 
         *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
       }
     }
-    if (more && l16 == 0) bad |= m5p_bad<NCH, VW>(c2, cy2);
+    if (more) bad |= m5p_bad<NCH, VW>(c2, cy2);
     if (__ballot(bad) != 0 && (tid % kWave) == 0) atomicOr(a.status, (int)kStatusBadCounter);
   }
   __syncthreads();
