@@ -160,9 +160,11 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   const Chunk ck = a.chunks[at];
   const int R = ck.R, nk = ck.nk;
   if (a.kmask && !packed) {   // uniform
+    // every wave reads all the flags: a vote of the workgroup would take LDS
+    // beside the dynamic part, which may be all there is
     int sel = 0;
-    for (int j = tid; j < nk; j += TH) sel |= a.kmask[ck.k0 + j];
-    if (!__syncthreads_or(sel)) return;
+    for (int j = lane; j < nk; j += kWave) sel |= a.kmask[ck.k0 + j];
+    if (!__any(sel)) return;
   }
   // loads in issue order: this chunk's kernel records and the model (small,
   // needed first), then the first two steps of rows; whatever would wait on
