@@ -247,15 +247,24 @@ int ensure_stat_ws(sugg_ctx* ctx, sugg_plan* p) {
 
 // Whether the fit takes each row once for the set ("class") of optimisations
 // it is a before version of, instead of once per optimisation.  A class costs
-// a partial sum of its own, the pair list B/2 times the rows: with u ids in
-// use there are up to 2^u classes, taken when they hold 32 rows or more on
-// average.  Whole fits, classes against pairs, 128 events, ten ids, 4..10 per
-// kernel: 18 rows a class (64 kernels) 479 against 456 us, 37 rows 489
-// against 517, 147 rows 577 against 820, 590 rows 993 against 2415; six ids
-// (64 classes): 16 rows 397 against 409 us; 40 events, ten ids, 6 per kernel:
-// 8 rows 176 against 155 us, 32 rows 183 against 178.
-bool gram_classes(int64_t rows, int used_ids) {
-  return used_ids < 40 && ((int64_t)1 << used_ids) <= rows / 32;
+// a partial sum of its own (30, 92 or 313 KB for up to 64, 128 or 256 events),
+// the pair list B/2 times the rows: with u ids in use there are up to 2^u
+// classes, taken when they hold 32 rows or more on average, 48 up to 64 events.
+// Whole fits, classes against pairs, us: 128 events, ten ids, 4..10 per kernel,
+// 18 rows a class (64 kernels) 479 / 456, 37 rows 489 / 517, 147 rows 577 /
+// 820, 590 rows 993 / 2415; 13 ids, 8 per kernel, 32 rows 938 / 1022, 128 rows
+// 1731 / 3354; 16 ids, 8 per kernel, 32 rows 5244 / 6080; 256 events, 11 ids,
+// 32 rows 1003 / 1310; 40 events, ten ids, 6 per kernel, 8 rows 176 / 155, 32
+// rows 183 / 178; 64 events, 15 ids, 8 per kernel, 32 rows 1721 / 1537, 14 ids, 4
+// per kernel, 64 rows 617 / 963.  The partials stay within 2 GB or the bytes
+// that an FP64 copy of the counters would take, whichever is more (17 ids and
+// 4.2 M rows of 128 events, 12 per kernel: 10.5 GB and 18.8 ms, pairs 1.4 GB and
+// 16.8 ms).
+bool gram_classes(int64_t rows, int used_ids, int E) {
+  if (used_ids >= 40) return false;
+  const int64_t classes = (int64_t)1 << used_ids;
+  return classes <= rows / (E <= 64 ? 48 : 32) &&
+         classes * gram_stride(E) <= std::max<int64_t>((int64_t)1 << 28, rows * E);
 }
 
 // The row list of the fit in segments, and the optimisations of each run of
@@ -350,7 +359,7 @@ int prepare_fit(sugg_ctx* ctx, sugg_plan* p, hipStream_t s) {
   GramLists g;
   int used = 0;
   for (int o = 0; o < D; ++o) used += p->opt_pairs[o] > 0;
-  if (gram_classes(p->N, used)) gram_class_lists(p, g);
+  if (gram_classes(p->N, used, E)) gram_class_lists(p, g);
   else gram_pair_lists(p, g);
   // Chunks: two per compute unit, of at least 128 rows (a chunk's partial
   // sum, written and read back, costs about as much as 150 rows) and at most
@@ -373,7 +382,7 @@ int prepare_fit(sugg_ctx* ctx, sugg_plan* p, hipStream_t s) {
   };
   A(p->d_lcyc64, sizeof(double) * p->N);
   A(p->d_gram_partial, sizeof(double) * stride * work.size());
-  A(p->d_gram_slices, sizeof(double) * stride * D * gram_slices((int)work.size()));
+  A(p->d_gram_slices, sizeof(double) * stride * D * gram_slices((int)work.size(), D, E));
   A(p->d_reduced, sizeof(double) * stride * D);
   A(p->d_grows, sizeof(GramRow) * g.n);
   if (solve_workspace(E)) A(p->d_solveA, sizeof(double) * solve_workspace(E) * std::max(1, D));

@@ -262,9 +262,9 @@ template hipError_t launch_gram<float>(const GramArgs&, hipStream_t);
 template hipError_t launch_gram<double>(const GramArgs&, hipStream_t);
 
 // Sums of the chunks' partials per optimisation, in two launches, each in a
-// fixed order.  The first reads every partial once: a thread adds one element
-// of every chunk of its slice to the accumulators of the optimisations in the
-// chunk's mask (16 ids per workgroup; the mask is uniform).  The labels' rows
+// fixed order.  The first reads every partial once per 16 ids: a thread adds one
+// element of every chunk of its slice to the accumulators of the optimisations in
+// the chunk's mask (16 ids per workgroup; the mask is uniform).  The labels' rows
 // are per chunk (the j-th id of its mask), so row 0 of the label blocks takes
 // the row of the id it is summed for; rows other than that and the ones' are
 // not used.
@@ -322,12 +322,16 @@ __global__ void __launch_bounds__(256) gram_reduce2_kernel(const double* __restr
 }
 
 // Slices of the first launch: about 16 chunks each, so that 45 blocks of
-// elements (128 events) times the slices fill the chip.
-int gram_slices(int n_work) { return std::max(1, std::min(32, n_work / 16)); }
+// elements (128 events) times the slices fill the chip; their sums at most 256
+// MB (64 ids and 256 events: 12 slices of 20 MB in place of 32).
+int gram_slices(int n_work, int D, int E) {
+  const int most = (int)std::max<int64_t>(1, ((int64_t)1 << 25) / (std::max(D, 1) * gram_stride(E)));
+  return std::max(1, std::min({32, n_work / 16, most}));
+}
 
 hipError_t launch_gram_reduce(const GramArgs& a, int D, double* slices, double* reduced, hipStream_t s) {
   if (D <= 0) return hipSuccess;
-  const int nb = gram_blocks(a.E), G = gram_slices(a.n_work);
+  const int nb = gram_blocks(a.E), G = gram_slices(a.n_work, D, a.E);
   const int64_t stride = gram_stride(a.E);
   (void)hipGetLastError();  // report only this launch's status
   hipLaunchKernelGGL(gram_reduce_kernel, dim3((unsigned)(stride / 256), G, (D + kReduceIds - 1) / kReduceIds), dim3(256),

@@ -265,7 +265,7 @@ struct GramArgs {
 
 int gram_blocks(int E);       // block columns: E padded, and the labels' and ones' block
 int64_t gram_stride(int E);   // doubles of one lower triangle
-int gram_slices(int n_work);  // slices of the chunks' sums
+int gram_slices(int n_work, int D, int E);   // slices of the chunks' sums
 template <typename T>
 hipError_t launch_gram(const GramArgs& a, hipStream_t s);
 // sums of the chunks' partials per id into reduced [D, gram_stride] (the
