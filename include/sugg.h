@@ -109,12 +109,12 @@ SUGG_API int32_t sugg_plan_max_opts(const sugg_plan* plan); /* max B_k, or -1 */
  * are few large chunks) each take a chunk of consecutive whole kernels in
  * memory order (about sugg_plan_get_items rows, any mix of B) and stream,
  * compose and rank it.  The split form serves sugg_suggest and sugg_predict
- * without a grid, other calls then take the fused form with unroll 1.  A new
- * plan's shape is chosen from its rows, its largest kernel and E (streaming
- * chunks then have the largest kernel's size, 64 to 512 rows, more in large
- * batches, until sugg_plan_set_items; where that shape is the fused one for a
- * batch of 65,536 rows or more, its grid and masked passes still stream until
- * the shape is set or tuned).  Results do not depend on the shape. */
+ * without a grid, other calls then take the fused form with unroll 1.  Until
+ * the shape is set or tuned, each pass of a plan takes the form that suits it,
+ * by the rows, the kernels' sizes, D, E, the dtype and n_suggest (the reported
+ * shape is that of sugg_suggest when the plan was made); streaming chunks then
+ * have the largest kernel's size, 64 to 512 rows, more in large batches, until
+ * sugg_plan_set_items.  Results do not depend on the shape. */
 SUGG_API int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int32_t grid);
 SUGG_API int32_t sugg_plan_get_launch(const sugg_plan* plan, int32_t* waves, int32_t* unroll, int32_t* grid);
 

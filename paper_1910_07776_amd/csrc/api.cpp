@@ -81,40 +81,90 @@ void build_items(const std::vector<int32_t>& nopts, const std::vector<int64_t>& 
   }
 }
 
-// Launch shape of a new plan's scoring kernel, from the batch's rows and its
-// largest kernel; chunk: rows of a streaming chunk.
-// - From 65,536 rows, and where a kernel has 128 versions or more, the
-//   streaming form, chunks of the largest kernel's size (64 to 512 rows; from
-//   524,288 rows, where there are enough chunks, at least 128: 8192 kernels of
-//   64 versions 56.8 against 51.0 us, 16,384 of 16..64 86 / 72).  us
-//   per pass, fused shape (4 waves, 2 rows a stage) against this one, 128
-//   FP32 events: 16,384 kernels of 4..10 optimisations 493 / 441, 4096 169 /
-//   113, 256 40 / 22; 64 versions x 8192 95 / 44, x 2048 19.0 / 17.5; 16 x
-//   65,536 162 / 132; 256 x 2048 95 / 46, x 16 16.1 / 12.9; 1024 x 4096 429 /
-//   383.  40 events, 4096 kernels of 4..10 107 / 47; 128 FP64 events, 256 of
-//   4..8 36 / 30.
-//   Lanes of more than 32 bytes of a row take 128 from 131,072 rows: 256 FP32
-//   events, 130,000 rows of 64 versions 31.8 / 26.1, 450,000 97 / 85.
-// - But FP32 batches of kernels of up to 64 versions whose items are all
-//   resident at once (resident_items) stay fused, 4 waves, 2 rows a stage:
-//   128 events, 66,000 rows of 16 versions 17.6 (streaming) / 14.0, 130,000
-//   28.2 / 18.4, 260,000 of 16..64 38.9 / 33.4; 40 events 21.3 / 14.0 at
-//   130,000; a second round of items costs 40 us (300,000 rows 53 / 71).
-// - Smaller batches of smaller kernels: the fused form with 8 waves a
-//   workgroup where a lane holds at most 32 bytes of a row (one or two rows a
-//   stage), else 4 waves: 64 versions x 1 kernel 7.8 against 6.3 us, x 64 7.4
-//   against 6.6, x 512 9.0 against 7.5; 2 kernels of 40 FP64 events 10.0
-//   against 8.6; 256 FP32 events the other way round, 19.0 against 9.9.
-PathLaunch default_launch(int64_t rows, int Bmax, int E, int dtype, int& chunk) {
-  const int lane_bytes = (dtype == SUGG_F32 ? 4 : 8) * (E <= 64 ? 4 : E <= 128 ? 8 : 16);
-  chunk = std::min(std::max(1 << Bmax, rows >= (lane_bytes > 32 ? 1 << 17 : 1 << 19) ? 128 : 64), 512);
-  if (rows >= 65536 || Bmax >= 7) return PathLaunch{4, -2, 0};
-  if (lane_bytes > 32) return PathLaunch{4, 2, 0};
-  return PathLaunch{8, dtype == SUGG_F32 ? 1 : 2, 0};
+// Rows of a streaming chunk: the largest kernel's size (64 to 512 rows; from
+// 524,288 rows, where there are enough chunks, at least 128: 8192 kernels of 64
+// versions 56.8 against 51.0 us, 16,384 of 16..64 86 / 72; lanes of more than 32
+// bytes of a row from 131,072 rows: 256 FP32 events, 130,000 rows of 64 versions
+// 31.8 / 26.1, 450,000 97 / 85).
+int row_bytes(const sugg_plan* p) {   // as the lanes hold it, padded
+  return (p->dtype == SUGG_F32 ? 4 : 8) * (p->E <= 64 ? 64 : p->E <= 128 ? 128 : 256);
 }
 
+int default_chunk(const sugg_plan* p) {
+  return std::min(std::max(1 << p->Bmax, p->N >= (row_bytes(p) > 512 ? 1 << 17 : 1 << 19) ? 128 : 64), 512);
+}
+
+// All work items of the fused form on the device at once (4 waves a workgroup).
 bool resident_items(const sugg_plan* p) {
-  return p->dtype == SUGG_F32 && p->E <= 128 && p->Bmax <= 6 && p->N >= 65536 && p->n_items <= 4 * p->cus;
+  return p->dtype == SUGG_F32 && p->E <= 128 && p->Bmax <= 6 && p->N >= 65536 &&
+         p->n_items <= (p->E <= 64 ? 5 : 4) * p->cus;
+}
+
+// Smaller batches of smaller kernels: always the fused form.
+bool small_batch(const sugg_plan* p) { return p->N < 65536 && p->Bmax < 7; }
+
+// Whether a pass takes the streaming form, from the set shape or, on a plan
+// whose shape was not set, from the batch's rows and kernels; n: length of the
+// pass's lists (0: none).  Times in us, fused form (4 waves, 2 rows a stage)
+// against streaming.
+//
+// From 65,536 rows, and where a kernel has 128 versions or more, streaming.  128
+// FP32 events: 16,384 kernels of 4..10 optimisations 493 / 441, 4096 169 / 113,
+// 256 40 / 22; 64 versions x 8192 95 / 44, x 2048 19.0 / 17.5; 16 x 65,536 162 /
+// 132; 256 x 2048 95 / 46, x 16 16.1 / 12.9; 1024 x 4096 429 / 383.  40 events,
+// 4096 kernels of 4..10 107 / 47; 128 FP64 events, 256 of 4..8 36 / 30.  But:
+// - FP32 batches of kernels of up to 64 versions whose items are all resident at
+//   once stay fused: 128 events, 66,000 rows of 16 versions 14.0 / 17.6, 130,000
+//   18.4 / 28.2, 260,000 of 16..64 33.4 / 38.9; 64 events, 300,000 rows of 16 24
+//   / 43, of 64 24 / 28; a second round of items costs 40 us (128 events, 300,000
+//   rows 71 / 53).
+// - So do small kernels: a streaming wave ranks its kernels one after another
+//   (three times the work for lists of more than 4).  Fewer than 8 versions on
+//   average: 500,000 rows of 1..4 and 64 events 98 / 242, 100,000 and 256 events
+//   47 / 87.  Fewer than 12, from 262,144 rows: 500,000 of 4..16 and 128 events
+//   98 / 110, 2 million 273 / 347; 70,000 and 256 events 44 / 37.  Fewer than 24,
+//   large batches: of 16 and 128 events, 1 million rows 162 / 132, 2 million 249
+//   / 284; 256 events, 260,000 rows equal, 1 million 208 / 243; 128 FP64 events,
+//   100,000 64 / 60, 300,000 128 / 146.  Lists of 8, of 16 and 128 events, 1
+//   million rows 165 / 254; of 16..64, 3 million 359 / 443.
+// - And kernels of up to 64 versions beside a model of more than 48 KB: every
+//   chunk stages it, and fewer than three workgroups share a compute unit.  64
+//   ids and 256 FP32 events, 64 versions: 100,000 rows 46 / 50, 1 million 211 /
+//   260, of 128 versions 237 / 246; 40 ids and 256 FP64 events 924 / 1019; 64
+//   ids and 128 FP64 events 100,000 rows 70 / 65, 300,000 128 / 132, 1 million 360
+//   / 388.  (32 ids and 256 FP64 events, 1 million: 652 / 637.)
+// The grid, without lists, streams but for the last of these and FP32 (1 million
+// rows 295 / 344; 2 million of 1..4 versions 190 / 120).  A masked pass streams
+// but for very small kernels (a quarter selected, 128 FP32 events, 500,000 rows
+// of 4 92 / 119, of 2..8 97 / 81; FP64 of 4 132 / 105, of 1..4 184 / 206), small
+// ones in resident batches (100,000 rows of 16 13 / 17) and long lists in large
+// batches (3 million rows of 16, lists of 8, 325 / 380).
+bool streams(const sugg_plan* p, bool grid, bool masked, int n) {
+  if (!p->auto_form) return p->cfg.unroll < 0;
+  if (small_batch(p)) return false;
+  const int64_t N = p->N, K = p->K, lists = n > 4 ? 3 : n > 0 ? 1 : 0;
+  const bool f32 = p->dtype == SUGG_F32, narrow = row_bytes(p) <= 512;
+  const int64_t w = (int64_t)p->D * row_bytes(p);
+  const bool model = p->D > 32 && w > 48 * 1024, many = N >= 1 << 19;
+  if (grid) return !(model && f32 && many && p->Bmax <= 7);
+  const bool resident = resident_items(p);
+  if (masked)
+    return 2 * N >= (f32 ? 9 : 6) * K && !(resident && N < 20 * K) && !(n > 4 && N < 18 * K && N >= 3 << 19);
+  if (resident || N < 8 * lists * K || (N < 12 * lists * K && N >= 1 << 18) ||
+      (N < 24 * lists * K && N > (!f32 ? 1 << 18 : narrow ? 3 << 19 : 400000)))
+    return false;
+  return !(model && (p->Bmax <= 6 ? f32 || w > 64 * 1024 || N >= 1 << 18 : p->Bmax == 7 && f32 && many));
+}
+
+// A new plan's shape.  Smaller batches of smaller kernels: the fused form with 8
+// waves a workgroup where a lane holds at most 32 bytes of a row (one or two
+// rows a stage), else 4 waves: 64 versions x 1 kernel 7.8 against 6.3 us, x 64
+// 7.4 against 6.6, x 512 9.0 against 7.5; 2 kernels of 40 FP64 events 10.0
+// against 8.6; 256 FP32 events the other way round, 19.0 against 9.9.
+void default_launch(sugg_plan* p, int n) {
+  p->auto_form = true;
+  if (small_batch(p)) p->cfg = row_bytes(p) > 512 ? PathLaunch{4, 2, 0} : PathLaunch{8, p->dtype == SUGG_F32 ? 1 : 2, 0};
+  else p->cfg = PathLaunch{4, streams(p, false, false, n) ? -2 : 2, 0};
 }
 
 // Wide workgroups for the streaming form where its chunks are large and few:
@@ -506,7 +556,7 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
   a.status = ctx->d_status;
   if (p->cfg.unroll == 0 && p->split_ok() && !grid && !kmask)
     return ctx->hip(launch_path_split<T>(a, p->d_arrivals, (T*)p->d_split_edges, s), "scoring kernel");
-  if ((p->cfg.unroll < 0 || (p->stream_others && (grid || kmask))) &&
+  if (streams(p, grid != nullptr, kmask != nullptr, idx ? n : 0) &&
       path_chunk_lds(sizeof(T), ctx->D, p->E, p->chunk_max_rows, p->chunk_max_nk) <= kLdsPerWorkgroup) {
     ChunkArgs<T> ch;
     ch.counters = c;
@@ -524,6 +574,7 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
     ch.max_nk = p->chunk_max_nk;
     ch.wide = wide_chunks(p, kmask != nullptr) ? 1 : 0;
     ch.kmask = kmask;
+    ch.packed = kmask && p->chunk_max_nk <= 16 && p->K <= 8ll * p->n_chunks ? 1 : 0;
     ch.grid = grid;
     ch.grid_ld = p->Bmax;
     ch.table = table;
@@ -536,7 +587,8 @@ int run_path(sugg_ctx* ctx, const sugg_plan* p, const T* c, const T* cyc, T* gri
     return ctx->hip(launch_path_chunks<T>(ch, p->cfg.unroll < 0 ? -p->cfg.unroll : 2, s), "scoring kernel (streaming form)");
   }
   PathLaunch cfg = p->cfg;
-  if (cfg.unroll <= 0) cfg.unroll = 1;   // the split or streaming form does not apply: fused, one row per stage
+  // the split or streaming form does not apply: fused, a new plan's two rows per stage or one
+  if (cfg.unroll <= 0) cfg.unroll = cfg.unroll == -2 ? 2 : 1;
   return ctx->hip(launch_path<T>(a, p->max_item_rows, p->max_item_kernels, std::max(1, p->Bmax), cfg, s),
                   "scoring kernel");
 }
@@ -726,13 +778,8 @@ int32_t sugg_plan_create(sugg_ctx* ctx, int32_t K, int32_t E, int32_t D, int32_t
   int target = 256;
   while (target > 64 && p->N / target < 2 * cus) target >>= 1;
   p->stat_chunks = colstats_chunks(std::max<int64_t>(p->N, 1));
-  int chunk = target;
-  p->cfg = default_launch(p->N, p->Bmax, E, dtype, chunk);
-  hipError_t e = plan_items(p, target, chunk);
-  if (e == hipSuccess && p->cfg.unroll < 0 && resident_items(p)) {
-    p->cfg = PathLaunch{4, 2, 0};
-    p->stream_others = true;
-  }
+  hipError_t e = plan_items(p, target, default_chunk(p));
+  default_launch(p, ctx->params.n_suggest);
   if (e == hipSuccess) e = upload(p->d_row_off, p->row_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_off, p->opt_off.data(), sizeof(int64_t) * (K + 1));
   if (e == hipSuccess) e = upload(p->d_opt_ids, p->opt_ids.data(), sizeof(int32_t) * nid);
@@ -1130,7 +1177,7 @@ int32_t sugg_plan_set_launch(sugg_plan* plan, int32_t waves, int32_t unroll, int
   if (waves < 1 || waves > 8 || grid < 0) return SUGG_E_ARG;
   if (unroll != 0 && unroll != 1 && unroll != 2 && unroll != 4 && unroll != -1 && unroll != -2 && unroll != -4)
     return SUGG_E_ARG;
-  plan->stream_others = false;
+  plan->auto_form = false;
   plan->cfg.waves = waves;
   plan->cfg.unroll = unroll;
   plan->cfg.grid = grid;
@@ -1178,6 +1225,8 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
   if (e == hipSuccess) e = hipEventCreate(&e0);
   if (e == hipSuccess) e = hipEventCreate(&e1);
   const PathLaunch keep = plan->cfg;
+  const bool keep_auto = plan->auto_form;
+  plan->auto_form = false;   // the candidates as they are, then the tuned shape for every pass
   const int keep_items = plan->item_rows, keep_chunk = plan->chunk_rows;
   const auto set_items = [&](int items, int chunk) -> hipError_t {
     return plan->item_rows != items || plan->chunk_rows != chunk ? plan_items(plan, items, chunk) : hipSuccess;
@@ -1269,7 +1318,7 @@ int32_t sugg_autotune(sugg_ctx* ctx, sugg_plan* plan, const void* counters, cons
     }
   }
   plan->cfg = e == hipSuccess ? best : keep;
-  if (e == hipSuccess) plan->stream_others = false;   // the tuned shape for every pass
+  if (e != hipSuccess) plan->auto_form = keep_auto;
   const hipError_t e2 = e == hipSuccess ? set_items(best_items, best_items) : set_items(keep_items, keep_chunk);
   if (e == hipSuccess) e = e2;
   if (e0) (void)hipEventDestroy(e0);

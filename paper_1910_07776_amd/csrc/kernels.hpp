@@ -134,6 +134,8 @@ struct ChunkArgs {
   int32_t max_nk;            // most kernels in a chunk
   int32_t wide;              // nonzero: workgroups of 1024 (or 512) threads, one row per lane group and stage
   const int32_t* kmask;      // [K] or null: only kernels with kmask != 0 are scored and written
+  int32_t packed;            // with kmask: workgroups go to the chunks with a selected kernel (each lane
+                             //   reads the flags of a chunk)
   T* grid;                   // [N, grid_ld] or null (then no ranking)
   int32_t grid_ld;
   T* table;                  // nullable

@@ -24,7 +24,6 @@ namespace sugg {
 // more than 32 bytes of a row, for its registers), which ends a large chunk
 // sooner where there are too few chunks to fill the chip.
 constexpr int kChunkThreads = 256;
-constexpr int kPackedNk = 16;   // masked passes: most kernels of a chunk whose flags a lane reads
 template <typename T, int VPL>
 constexpr int chunk_wide() { return sizeof(T) * VPL <= 32 ? 1024 : 512; }
 
@@ -89,8 +88,9 @@ __device__ __forceinline__ VecN<T, 16 / sizeof(T)> weight_vec(const T* W, int ld
 // spread evenly over the chip, and the others end at once (28% of 4096 kernels
 // of 1024 versions: 178 us with one workgroup per chunk and each row's flag
 // read from memory, 174 with the packing, 132 with the flags in LDS too).
-// Chunks of many small kernels stay one workgroup each: reading 64 chunks'
-// flags would cost more than it evens out.
+// Chunks of many small kernels (over 16, or 8 on average) stay one workgroup
+// each: reading 64 chunks' flags would cost more than it evens out (250,000
+// kernels of 8 versions, a quarter selected: 293 us packed, 212 not).
 template <typename T, int VPL, int VW, int U, int KT, bool FULL, int TH, bool GRID>
 __global__ void __launch_bounds__(TH) __attribute__((amdgpu_waves_per_eu(
     TH == 1024 && sizeof(T) == 4 ? 8 : 1)))   // two wide FP32 workgroups per compute unit
@@ -144,7 +144,7 @@ path_chunk_kernel(const ChunkArgs<T> a) {
   const int4* recs = reinterpret_cast<const int4*>(a.recs);
   int4* krv = reinterpret_cast<int4*>(kr);
   int at = blockIdx.x;
-  const bool packed = a.kmask && a.max_nk <= kPackedNk;   // uniform
+  const bool packed = a.packed != 0;   // uniform
   if (packed) {
     const int nseg = (a.n_chunks + kWave - 1) / kWave, seg = at % nseg, i = seg * kWave + lane;
     int sel = 0;
@@ -367,7 +367,7 @@ hipError_t launch_chunk_k(const ChunkArgs<T>& a, size_t smem, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   (void)hipGetLastError();  // report only this launch's status
-  const int grid = a.kmask && a.max_nk <= kPackedNk ? (a.n_chunks + kWave - 1) / kWave * kWave : a.n_chunks;
+  const int grid = a.packed ? (a.n_chunks + kWave - 1) / kWave * kWave : a.n_chunks;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(TH), smem, s, a);
   return hipGetLastError();
 }

@@ -81,7 +81,7 @@ struct sugg_plan {
   int uni_ops = 0;
   uint64_t uni_opt_lo = 0, uni_opt_hi = 0;
   sugg::PathLaunch cfg{4, 2, 0};   // launch shape of the scoring kernel (default_launch, set, or autotuned)
-  bool stream_others = false;      // a fused default whose grid and masked passes take the streaming form
+  bool auto_form = true;           // not set: each pass's form by the batch (streams)
   int item_rows = 256;             // target rows of a work item (autotuned)
   int chunk_rows = 256;            // and of a chunk (item_rows once either is set)
   // statistics workspace
