@@ -96,7 +96,8 @@ hipError_t launch_ibk_labels(const T* cycles, const int32_t* before, const int32
 
 // ---- samples in matrix-core order ------------------------------------------------
 // hi + lo of x (already scaled): the nearest FP16 and the nearest FP16 of the
-// rest; |x - hi - lo| <= 2^-23 |x| above FP16's subnormal range.
+// rest; |x - hi - lo| <= 2^-23 |x| + 2^-25 (the second part where lo is below
+// FP16's normal range).
 __device__ __forceinline__ void split_f16(float x, _Float16& hi, _Float16& lo) {
   hi = (_Float16)x;
   lo = (_Float16)(x - (float)hi);
@@ -566,8 +567,10 @@ __global__ void __launch_bounds__(256) ibk_refine_kernel(const IbkKnnArgs a) {
   ibk_query64<T, NC, VW>(a, qr, l16, qv);
   // err(u) = 2 sqrt(u) Dz + Dz^2 + eps span(u)^2 + 1e-12 (1 + u): Dz bounds
   // the rounding of query minus sample vectors (the query's FP32 rounding,
-  // measured here, plus the stored vectors' worst, plus 2^-22.4 of both for
-  // the split), span the sum of the two vectors' norms.  eps: 2^-24 per FP32
+  // measured here, plus the stored vectors' worst, with their halves' loss
+  // below FP16's normal range, plus 2^-22.4 of both for the split; a query has
+  // a scale of its own, so its loss there is below 2^-34 of it), span the sum
+  // of the two vectors' norms.  eps: 2^-24 per FP32
   // addition, three products per feature (2 q.t <= span^2 / 2, every addition
   // allowed twice the rounding), the two norms' sums and two more; lo.lo,
   // left out, is at most 2^-22 span^2 / 2.

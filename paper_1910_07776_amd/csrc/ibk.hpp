@@ -28,8 +28,10 @@ struct IbkModel {
   float inv_scale = 1.0f;      // power of two
   double* Z64 = nullptr;       // [Ntr, E] FP64 standardised training rows (exact distances)
   int32_t* srow = nullptr;     // [Ns] training row of each sample (its before version)
-  double dt_norm = 0.0;        // Euclidean norm over columns of max_rows |Z32 - Z64|: the
-                               //   FP32 rounding of any stored vector is at most this
+  double dt_norm = 0.0;        // Euclidean norm over columns of max_rows |Z32 - Z64|, and sqrt(E) 2^-25 / scale:
+                               //   the FP32 rounding of any stored vector and what its halves lose below
+                               //   FP16's normal range (where the training set's largest value sets the
+                               //   scale far above the vector) are at most this
   float* norm = nullptr;       // [tiles * 32] their squared norms, infinite for the fill of a last tile
   int32_t* d_toff = nullptr;   // [D+1] first tile of each id
   int32_t* sidx = nullptr;     // [tiles * 32] the sample (within its id) in each slot, -1: fill

@@ -154,6 +154,8 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
     (void)std::frexp(zmax > 0.0f ? zmax : 1.0f, &x);
     x = std::min(std::max(x, -85), 115);
     m->inv_scale = std::ldexp(1.0f, x - 15);
+    // halves below FP16's normal range are off by up to 2^-25 of the scaled value
+    m->dt_norm += std::sqrt((double)E) * std::ldexp((double)m->inv_scale, -25);
     e = launch_ibk_pack(zrows, m->srow, m->d_off, m->d_toff, d_step, p->D, n_tiles, m->Epad, std::ldexp(1.0f, 15 - x),
                         m->Zt, m->norm, m->sidx, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);   // zrows is freed
