@@ -25,33 +25,35 @@ namespace sugg {
 constexpr int kM5pThreads = kM5pRows * kRowLanes;
 
 // Lane l16's chunks of a row, columns (l16 + 16 ch) * VW + [0, VW), read in
-// the plan dtype and widened to FP64 (1 past E).
-template <typename TI, int NCH, int VW>
-__device__ __forceinline__ void m5p_load_row(const TI* rp, int E, int l16, double (&c)[NCH][VW]) {
+// the plan dtype (1 past E), widened to FP64 where they are used.
+template <typename TI, int NCH, int VW, typename TO>
+__device__ __forceinline__ void m5p_load_row(const TI* rp, int E, int l16, TO (&c)[NCH][VW]) {
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch) {
     const int c0 = (l16 + kRowLanes * ch) * VW;
     if (c0 + VW <= E) {
       const VecN<TI, VW> q = *reinterpret_cast<const VecN<TI, VW>*>(rp + c0);
 #pragma unroll
-      for (int v = 0; v < VW; ++v) c[ch][v] = (double)q.v[v];
+      for (int v = 0; v < VW; ++v) c[ch][v] = (TO)q.v[v];
     } else {
 #pragma unroll
-      for (int v = 0; v < VW; ++v) c[ch][v] = c0 + v < E ? (double)rp[c0 + v] : 1.0;
+      for (int v = 0; v < VW; ++v) c[ch][v] = c0 + v < E ? (TO)rp[c0 + v] : TO(1);
     }
   }
 }
 
 // row_features' check without the logarithms: those of a row are all finite
-// where its counters and cycles are positive and finite.
-template <int NCH, int VW>
-__device__ __forceinline__ bool m5p_bad(const double (&c)[NCH][VW], double cy) {
-  auto ok = [](double v) { return v > 0.0 && v < __builtin_huge_val(); };
-  bool bad = !ok(cy);
+// where its counters and cycles are positive and finite (one class test each:
+// positive normal or subnormal).
+__device__ __forceinline__ bool m5p_ok(float v) { return __builtin_amdgcn_classf(v, 0x180); }
+__device__ __forceinline__ bool m5p_ok(double v) { return __builtin_amdgcn_class(v, 0x180); }
+template <typename TI, int NCH, int VW>
+__device__ __forceinline__ bool m5p_bad(const TI (&c)[NCH][VW], TI cy) {
+  bool bad = !m5p_ok(cy);
 #pragma unroll
   for (int ch = 0; ch < NCH; ++ch)
 #pragma unroll
-    for (int v = 0; v < VW; ++v) bad |= !ok(c[ch][v]);
+    for (int v = 0; v < VW; ++v) bad |= !m5p_ok(c[ch][v]);
   return bad;
 }
 
@@ -127,24 +129,24 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
     const int S = S0 + g;
     const bool live = S < (1 << B), need = m5p_row_edges(S, B, grid) > 0;
     bool bad = false;
-    if (live) {
-      T c[NCH][VW];
+    if (live && !need) {
+      TI c[NCH][VW];
+      m5p_load_row<TI, NCH, VW>(a.counters + (r0 + S) * a.E, a.E, l16, c);
+      bad = m5p_bad<TI, NCH, VW>(c, a.cycles[r0 + S]);
+    }
+    if (need) {
+      T c[NCH][VW], s_r[NCH][VW], m_r[NCH][VW], z[NCH][VW];
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + S) * a.E, a.E, l16, c);
       const T cy = (T)a.cycles[r0 + S];
-      if (need) {
-        T s_r[NCH][VW], m_r[NCH][VW], z[NCH][VW];
-        column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
-        const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
-        bad = !__builtin_isfinite(chk);
+      column_constants<T, NCH, VW, false>(a.mu, a.isg, a.E, l16, s_r, m_r);
+      const T chk = row_features<T, NCH, VW>(c, cy, s_r, m_r, z);
+      bad = !__builtin_isfinite(chk);
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-          VecN<T, VW> q;
+      for (int ch = 0; ch < NCH; ++ch) {
+        VecN<T, VW> q;
 #pragma unroll
-          for (int v = 0; v < VW; ++v) q.v[v] = z[ch][v];
-          *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
-        }
-      } else {
-        bad = m5p_bad<NCH, VW>(c, cy);
+        for (int v = 0; v < VW; ++v) q.v[v] = z[ch][v];
+        *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
       }
     }
     if (__ballot(bad) != 0 && (tid % kWave) == 0) atomicOr(a.status, (int)kStatusBadCounter);
@@ -236,14 +238,15 @@ __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const 
   if (tid + 1 < V) root = ids[31 - __clz(tid + 1)];
   {
     const bool own = g < half, more = half + g < V;   // uniform per group; for V >= 8 per wave
-    T c[NCH][VW], c2[NCH][VW], cy = T(1), cy2 = T(1);
+    T c[NCH][VW], cy = T(1);
+    TI c2[NCH][VW], cy2 = TI(1);
     if (own) {
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + g) * a.E, a.E, l16, c);
       cy = (T)a.cycles[r0 + g];
     }
     if (more) {
       m5p_load_row<TI, NCH, VW>(a.counters + (r0 + half + g) * a.E, a.E, l16, c2);
-      cy2 = (T)a.cycles[r0 + half + g];
+      cy2 = a.cycles[r0 + half + g];
     }
     if (tid + 1 < V) root = a.root[root];
     T s_r[NCH][VW], m_r[NCH][VW];
@@ -261,7 +264,7 @@ __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const 
         *reinterpret_cast<VecN<T, VW>*>(&zl[g][(l16 + kRowLanes * ch) * VW]) = q;
       }
     }
-    if (more) bad |= m5p_bad<NCH, VW>(c2, cy2);
+    if (more) bad |= m5p_bad<TI, NCH, VW>(c2, cy2);
     if (__ballot(bad) != 0 && (tid % kWave) == 0) atomicOr(a.status, (int)kStatusBadCounter);
   }
   __syncthreads();
