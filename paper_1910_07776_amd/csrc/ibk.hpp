@@ -27,14 +27,15 @@ struct IbkModel {
                                //   matrix-core order (ibk_pack_kernel), scaled by 1 / inv_scale
   float inv_scale = 1.0f;      // power of two
   double* Z64 = nullptr;       // [Ntr, E] FP64 standardised training rows (exact distances)
-  int32_t* srow = nullptr;     // [Ns] training row of each sample (its before version)
+  int32_t* srow = nullptr;     // [Ns] training row of each sample (its before version), then d_toff
+                               //   and [D] the order of each id's samples (see ibk_pack_kernel)
   double dt_norm = 0.0;        // Euclidean norm over columns of max_rows |Z32 - Z64|, and sqrt(E) 2^-25 / scale:
                                //   the FP32 rounding of any stored vector and what its halves lose below
                                //   FP16's normal range (where the training set's largest value sets the
                                //   scale far above the vector) are at most this
   float* norm = nullptr;       // [tiles * 32] their squared norms, infinite for the fill of a last tile
-  int32_t* d_toff = nullptr;   // [D+1] first tile of each id
-  int32_t* sidx = nullptr;     // [tiles * 32] the sample (within its id) in each slot, -1: fill
+  int32_t* d_toff = nullptr;   // [D+1] first tile of each id (behind srow)
+  int32_t* sidx = nullptr;     // (behind norm) [tiles * 32] the sample (within its id) in each slot, -1: fill
   double* y = nullptr;         // [Ns] ln cyc(before) - ln cyc(after)
   int64_t* d_off = nullptr;    // [D+1]
   double* mu64 = nullptr;      // [E] training column means of ln(c / cyc)

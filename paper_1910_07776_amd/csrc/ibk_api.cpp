@@ -18,7 +18,7 @@ using namespace sugg;
 
 void ibk_model_free(IbkModel*& m) {
   if (!m) return;
-  dfree(m->Zt); dfree(m->d_toff); dfree(m->sidx); dfree(m->Z64); dfree(m->srow); dfree(m->norm); dfree(m->y); dfree(m->d_off);
+  dfree(m->Zt); dfree(m->Z64); dfree(m->srow); dfree(m->norm); dfree(m->y); dfree(m->d_off);
   dfree(m->mu64); dfree(m->sig64); dfree(m->mu_t); dfree(m->isg_t);
   delete m;
   m = nullptr;
@@ -81,13 +81,13 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
   for (int o = 0; o < p->D; ++o) m->off[o + 1] = m->off[o] + (int64_t)bef[o].size();
   m->Ns = m->off[p->D];
   std::vector<int32_t> hb, ha;
-  hb.reserve(m->Ns);
+  hb.reserve(m->Ns + 2 * p->D + 1);
   ha.reserve(m->Ns);
   for (int o = 0; o < p->D; ++o) {
     hb.insert(hb.end(), bef[o].begin(), bef[o].end());
     ha.insert(ha.end(), aft[o].begin(), aft[o].end());
   }
-  int32_t *d_after = nullptr, *d_step = nullptr;
+  int32_t* d_after = nullptr;
   double* partial = nullptr;
   float* zrows = nullptr;
   const int chunks = colstats_chunks(std::max<int64_t>(p->N, 1));
@@ -103,6 +103,9 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
     while (std::gcd(q, std::max<int64_t>(n, 1)) != 1) ++q;
     step[o] = (int32_t)q;
   }
+  // srow, the tiles' offsets and the steps in one array
+  hb.insert(hb.end(), toff.begin(), toff.end());
+  hb.insert(hb.end(), step.begin(), step.end());
   const int64_t n_tiles = toff[p->D], slots = std::max<int64_t>(n_tiles, 1) * kIbkTile;
   hipError_t e = hipMalloc((void**)&m->mu64, sizeof(double) * E);
   if (e == hipSuccess) e = hipMalloc((void**)&m->sig64, sizeof(double) * E);
@@ -111,11 +114,11 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
   if (e == hipSuccess) e = hipMalloc((void**)&partial, sizeof(double) * 2 * E * chunks);
   if (e == hipSuccess) e = hipMalloc((void**)&zrows, sizeof(float) * (size_t)p->N * m->Epad);
   if (e == hipSuccess) e = hipMalloc((void**)&m->Zt, 2 * sizeof(_Float16) * (size_t)slots * m->Epad);
-  if (e == hipSuccess) e = hipMalloc((void**)&m->norm, sizeof(float) * (size_t)slots);
-  if (e == hipSuccess) e = hipMalloc((void**)&m->sidx, sizeof(int32_t) * (size_t)slots);
-  if (e == hipSuccess) e = upload_vec(m->d_toff, toff);
-  if (e == hipSuccess) e = upload_vec(d_step, step);
+  if (e == hipSuccess) e = hipMalloc((void**)&m->norm, (sizeof(float) + sizeof(int32_t)) * (size_t)slots);
   if (e == hipSuccess) e = upload_vec(m->srow, hb);
+  m->sidx = reinterpret_cast<int32_t*>(m->norm + slots);
+  m->d_toff = m->srow + m->Ns;
+  const int32_t* d_step = m->d_toff + p->D + 1;
   if (e == hipSuccess) e = hipMalloc((void**)&m->Z64, sizeof(double) * (size_t)std::max<int64_t>(p->N, 1) * E);
   if (e == hipSuccess) e = upload_vec(d_after, ha);
   if (e == hipSuccess) e = hipMalloc((void**)&m->y, sizeof(double) * ns1);
@@ -163,7 +166,6 @@ int fit_t(sugg_ctx* ctx, sugg_plan* p, const T* c, const T* cyc, int k, hipStrea
   dfree(dz);
   dfree(lcyc);
   dfree(d_after);
-  dfree(d_step);
   dfree(partial);
   dfree(zrows);
   if (e != hipSuccess) {
