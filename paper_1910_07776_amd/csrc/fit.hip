@@ -88,8 +88,9 @@ int64_t gram_stride(int E) { return (int64_t)gram_blocks(E) * (gram_blocks(E) + 
 // set of optimisations (gram_classes): 4.8 M rows in place of 21.5 M pairs on
 // the 16,384-kernel training set.  Features are formed here: their FP64 copy
 // (4.9 GB there) was written once and read back 4.5 times.
-// Measured on that set: 2.99 ms, where features and sums took 48.8 ms before;
-// 512 kernels of 64 versions: 38 us, before 223 us.
+// Measured on that set: 2.95 ms, where features and sums took 48.8 ms before;
+// 512 kernels of 64 versions: 36 us, before 223 us.  Beyond 128 events 14 to 33 of
+// the 256 registers spill (17 block columns of accumulators).
 template <typename T, int NB, int VW>
 __global__ void __launch_bounds__(NB <= 9 ? 256 : 512, 2) gram_kernel(const GramArgs a) {
   constexpr int W = NB <= 9 ? 4 : 8;            // waves per workgroup

@@ -212,9 +212,10 @@ __global__ void __launch_bounds__(kM5pThreads) m5p_kernel(const M5pArgs<TI> a) {
 // Bound by a chain of latencies (row addresses, rows, the walk's blocks, the
 // leaf's weights) with the FP64 logarithms between: with 256 threads and the
 // features of all 64 rows, 512 kernels of 64 versions and 128 FP32 events took
-// 20.9 us, 9.9 of it features; now 15.5 (the whole call 22.3 -> 15.8; 300 of 128
-// versions by tiles and a separate composition 42, now 26; 1000 of 16 with 200
-// events 48 -> 16).
+// 20.9 us, 9.9 of it features; now 15.4 (the whole call 22.1 -> 15.4, on counters
+// that are not in a cache 24.5 -> 16.6; 300 of 128 versions by tiles and a separate
+// composition 42, now 26; 1000 of 16 with 200 events 48 -> 16; 4096 of 64 145 ->
+// 88).  Beyond 128 events the instance for 128 versions spills 4 to 8 registers.
 template <typename TI, int VPL, int VW, int MB>
 __global__ void __launch_bounds__(kRowLanes << (MB - 1)) m5p_small_kernel(const M5pArgs<TI> a, TI* table,
                                                                           int32_t* idx_out, TI* score_out,

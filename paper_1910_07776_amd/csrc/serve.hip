@@ -11,8 +11,10 @@
 // ascending order afterwards.  Separate launches for ranking, band, judge and
 // contract took 15.9 + 6.0 + 35.7 + 5.9 us for 4096 kernels of 1024 versions
 // (the judge ran a wave per place of a list of up to 3 + 16, each workgroup
-// staging the weights); one takes 22.3.  Four waves a kernel: 26.2, with a
-// sorted list per lane and merges for the ranking 38.6.
+// staging the weights); one takes 16 to 22 (by the subsets that are listed).
+// A whole query of 64 kernels of 256 versions 53.9 -> 42.1, on counters that are
+// not in a cache 55.3 -> 45.2; of 512 61.6 -> 44.8 and 64.2 -> 47.3.  Four waves a
+// kernel: 26.2, with a sorted list per lane and merges for the ranking 38.6.
 #include <hip/hip_runtime.h>
 
 #include "kernels.hpp"
