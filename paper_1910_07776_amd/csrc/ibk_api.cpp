@@ -210,9 +210,9 @@ int build_queries(sugg_ctx* ctx, sugg_plan* p, const IbkModel* m, int mode) {
   q.per_opt.assign(D, 0);
   std::vector<int> order(D);
   for (int o = 0; o < D; ++o) order[o] = o;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    return m->off[x + 1] - m->off[x] > m->off[y + 1] - m->off[y];
-  });
+  // (a plan may name more ids than the model knows, if its kernels have none of them)
+  const auto samples = [&](int o) { return o < m->D ? m->off[o + 1] - m->off[o] : 0; };
+  std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return samples(x) > samples(y); });
   for (int o : order) {
     const int64_t base = (int64_t)hs.size();
     q.per_opt[o] = (int64_t)src[o].size();
