@@ -242,7 +242,9 @@ __device__ __forceinline__ void knn_insert(double (&l)[KT], double key) {
 // products; a large bf16 library product reaches 1.36 here).  Against FP64
 // the split's distances are closer than the FP32 products' were: on normal
 // vectors, rms error 1.2e-5 against 1.7e-5 at 128 features, 2.4e-5 against
-// 4.0e-5 at 256, 3.2e-6 against 3.7e-6 at 32 (the norms are summed in FP64).
+// 4.0e-5 at 256, 3.2e-6 against 3.7e-6 at 32 (the norms are summed in FP64); on
+// the features of twelve batches of perf/cases.py's ranges (40 to 128 events, a
+// query's nearest samples and random ones) its rms error is 0.61 to 0.86 of theirs.
 // Two workgroups per compute unit where the registers allow it without
 // spilling (up to 128 events with lists of at most 16), else one.
 template <int ES, int KT>
